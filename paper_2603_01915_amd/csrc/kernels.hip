@@ -713,44 +713,67 @@ struct TransSink {
     __device__ __forceinline__ void finish_lane(int32_t, int, bool) {}
 };
 
-// Position of element i of the LDS block of dX: one spare slot after every 32,
-// so that lanes whose columns lie a multiple of 32 / KC apart (equal lane
-// lengths over a regular row walk exactly such strides) do not all hit one
-// LDS bank.
-__device__ __forceinline__ uint32_t lds_slot(uint32_t i) { return i + (i >> 5); }
+// Position of column i in a plane of the LDS block of dX: a permutation within
+// every 32 columns that differs from one 32 to the next, so that lanes whose
+// columns lie a multiple of 32 apart (equal lane lengths over a regular row
+// walk exactly such strides) do not all hit one LDS bank pair.  Planes are
+// padded to a multiple of 32 columns.
+__device__ __forceinline__ uint32_t lds_slot(uint32_t i) { return i ^ ((i >> 5) & 31u); }
 
-// dX (k columns) += A^T dY into a block of dX in LDS (trans_lds_kernel);
-// alpha is applied when the copies are summed
+// dX[c0 .. c0 + cols) += A^T dY for up to KC columns of dY into a block of dX
+// in LDS (trans_lds_kernel); alpha is applied when the copies are summed.
+// The block is FP64 for either value type: what bounds the scatter is the
+// rate of LDS atomic adds, measured at 0.33 lane operations per clock and CU
+// for ds_add_f32 whatever the addresses, 2.9 (random addresses) to 6.4 (unit
+// stride) for ds_add_f64.
 template <typename VT, int KC>
 struct TransLdsSink {
     static constexpr bool kCoop = false;
     static constexpr bool kPairs = false;
     static constexpr int kOcc = 4;
     struct Params {
-        const VT *dY;
+        const VT *dY;     // the first column of this pass
         uint32_t lddy;
-        VT *lds;  // n x KC, set by the kernel
+        uint32_t width;   // columns of dY in this pass, at most KC
+        uint32_t c0, cols;  // columns of A (rows of dX) of this pass
+        uint32_t plane;   // elements of one column's plane in the block
+        double *lds;      // width planes, set by the kernel
     };
     const Params p;
     int32_t cur;
-    VT dy[KC];
+    double dy[KC];
     static __device__ __forceinline__ uint32_t col_scale(const Params &) { return 1u; }
     __device__ TransLdsSink(const Params &pp, int64_t, int32_t, bool) : p(pp), cur(-1) {}
     __device__ __forceinline__ void load_row(int32_t row) {
         cur = row;
         const VT *src = p.dY + (uint64_t)(uint32_t)row * p.lddy;
 #pragma unroll
-        for (int c = 0; c < KC; ++c) dy[c] = src[c];
+        for (int c = 0; c < KC; ++c)
+            if (c < (int)p.width) dy[c] = (double)src[c];  // uniform test
+    }
+    __device__ __forceinline__ void add(uint32_t col, VT v) {
+        const uint32_t i = col - p.c0;
+        if (i < p.cols) {
+            double *dst = p.lds + lds_slot(i);
+#pragma unroll
+            for (int c = 0; c < KC; ++c)
+                if (c < (int)p.width) unsafeAtomicAdd(dst + c * p.plane, (double)v * dy[c]);
+        }
     }
     template <bool MULTI>
     __device__ __forceinline__ void segment(const uint32_t col[4], const VT v[4], int nreal,
                                             int64_t, const int32_t rowk[4]) {
+        // common case of the whole wavefront: four nonzeros of the row at hand
+        if (!ballot(nreal < 4 || rowk[3] != cur)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) add(col[k], v[k]);
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             if (k < nreal) {
                 if (rowk[k] != cur) load_row(rowk[k]);
-#pragma unroll
-                for (int c = 0; c < KC; ++c) atomicAdd(p.lds + lds_slot(col[k] * KC + c), v[k] * dy[c]);
+                add(col[k], v[k]);
             }
     }
     __device__ __forceinline__ void pre_step() {}
@@ -1408,45 +1431,96 @@ __global__ __launch_bounds__(decode_max_threads(MINW), MINW) void decode_kernel(
     decode_sweep<LAYOUT, VT, Sink, TF>(a, sp, tb);
 }
 
+// The passes of a transposed product with dX privatised in LDS: pass p takes
+// the columns of dY from (p / blocks) * width on (width of them, the last pass
+// what is left) and the columns of A from (p % blocks) * cols on.
+struct TransPlan {
+    int64_t n;           // columns of A
+    int32_t k;           // columns of dY
+    int32_t width;       // columns of dY per pass
+    int32_t blocks;      // column blocks of A
+    int32_t cols, plane;  // columns of A per block; the same padded to a multiple of 32
+    int32_t pass0, passes;  // passes of this launch: pass0 .. pass0 + passes
+    __device__ __forceinline__ int32_t first(int32_t p) const { return p / blocks * width; }
+    __device__ __forceinline__ int32_t columns(int32_t p) const { return min(width, k - first(p)); }
+    __device__ __forceinline__ int32_t row0(int32_t p) const { return p % blocks * cols; }
+    __device__ __forceinline__ int32_t rows(int32_t p) const { return (int32_t)min((int64_t)cols, n - row0(p)); }
+};
+
 // Transposed product with dX privatised in LDS: a workgroup (one per CU)
-// scatters into its own copy of the n x KC block of dX with LDS atomic adds,
-// then writes it to part[blockIdx.x]; trans_reduce_kernel sums the copies.
-// No global atomics, so no contention when n is small (the tall pruned
-// weight: every column of dX receives thousands of contributions).
+// scatters into its own block of dX with LDS atomic adds, then writes it to
+// part[blockIdx.x]; trans_reduce_kernel sums the copies.  No global atomics,
+// so no contention when n is small (the tall pruned weight: every column of
+// dX receives thousands of contributions).  All passes run in one launch,
+// workgroup b on pass b % passes with its share of the encoded waves: the
+// copies to sum are then as many per pass as it has workgroups, and the
+// tables are staged once per workgroup.  Bound by decoding the streams once
+// per pass and by the LDS atomic adds (see TransLdsSink): pruned 11008 x 4096
+// weight, k = 16, 6 passes of up to 3 columns: 0.365 ms, reduction 5 us (FP32
+// adds in 4 passes of 4 columns: 4 x 0.64 ms, reductions 4 x 12 us).
 template <int LAYOUT, typename VT, int KC, int TF>
 __global__ __launch_bounds__(1024, 4) void trans_lds_kernel(DevMat a,
                                                             typename TransLdsSink<VT, KC>::Params sp,
-                                                            VT *part) {
+                                                            TransPlan tp, VT *part) {
     __shared__ __align__(16) Tables<VT> tb;
     extern __shared__ __align__(16) unsigned char s_dyn[];
-    VT *s_dx = (VT *)s_dyn;
-    const int64_t cnt = a.n * KC, slots = lds_slot((uint32_t)cnt);
-    for (int64_t i = threadIdx.x; i < slots; i += blockDim.x) s_dx[i] = (VT)0;
+    typename TransLdsSink<VT, KC>::Params q = sp;
+    q.lds = (double *)s_dyn;
+    const int32_t pb = (int32_t)(blockIdx.x % (uint32_t)tp.passes), p = tp.pass0 + pb;
+    q.dY += tp.first(p);
+    q.width = (uint32_t)tp.columns(p);
+    q.c0 = (uint32_t)tp.row0(p);
+    q.cols = (uint32_t)tp.rows(p);
+    q.plane = (uint32_t)tp.plane;
+    const uint32_t slots = q.width * q.plane;
+    for (uint32_t i = threadIdx.x; i < slots; i += blockDim.x) q.lds[i] = 0.0;
     // (the table staging inside the sweep ends with a barrier, which also
     // orders these stores before the first scatter)
-    typename TransLdsSink<VT, KC>::Params q = sp;
-    q.lds = s_dx;
-    decode_sweep<LAYOUT, VT, TransLdsSink<VT, KC>, TF>(a, q, tb);
+    typedef TransLdsSink<VT, KC> Sink;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const int64_t wpb = blockDim.x / kWave;
+    const int64_t groups = (gridDim.x - (uint32_t)pb + tp.passes - 1) / (uint32_t)tp.passes;  // of this pass
+    const int64_t stride = groups * wpb;
+    const int64_t s0 = blockIdx.x / (uint32_t)tp.passes * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t share = s0 < a.num_waves ? (a.num_waves - 1 - s0) / stride + 1 : 0;
+    if constexpr (LAYOUT == 2) {
+        stage_tables<VT>(a, tb, 1u);
+        for (int64_t s = s0, k = 0; s < a.num_waves; s += stride, ++k) {
+            set_progress_priority(share - k, share);
+            decode_slice_global<LAYOUT, VT, Sink, TF>(a, tb, s, lane, q);
+        }
+    } else {
+        decode_rows<VT, Sink, TF>(a, tb, lane, q, a.num_waves, s0, stride, share);
+    }
     __syncthreads();
-    VT *dst = part + (int64_t)blockIdx.x * cnt;
-    for (int64_t i = threadIdx.x; i < cnt; i += blockDim.x) dst[i] = s_dx[lds_slot((uint32_t)i)];
+    VT *dst = part + (int64_t)blockIdx.x * tp.width * tp.plane;
+    for (uint32_t i = threadIdx.x; i < slots; i += blockDim.x) {
+        const uint32_t c = i / q.plane, j = i - c * q.plane;
+        dst[i] = (VT)q.lds[c * q.plane + lds_slot(j)];
+    }
 }
 
-// dX (KC columns) = alpha * (sum of the G copies) + beta * dX
+// dX = alpha * (sum of the copies of its pass) + beta * dX for the columns of
+// this launch's passes; grid workgroups wrote the copies.  A thread per
+// element, consecutive threads on consecutive rows of dX (elements of a plane).
 template <typename VT>
-__global__ __launch_bounds__(256) void trans_reduce_kernel(const VT *part, int64_t G, int64_t n,
-                                                           int KC, VT *dX, int64_t lddx,
-                                                           double alpha, double beta) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, cnt = n * KC;
-    if (i >= cnt) return;
+__global__ __launch_bounds__(256) void trans_reduce_kernel(const VT *part, TransPlan tp, int32_t grid, VT *dX,
+                                                           int64_t lddx, double alpha, double beta) {
+    const int32_t pb = (int32_t)blockIdx.y, p = tp.pass0 + pb;
+    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    const int32_t c = i / tp.plane, j = i - c * tp.plane;
+    if (c >= tp.columns(p) || j >= tp.rows(p)) return;
+    const int64_t copy = (int64_t)tp.width * tp.plane, step = (int64_t)tp.passes * copy;
+    const VT *q = part + (int64_t)pb * copy + i;
+    const int32_t G = (grid - pb + tp.passes - 1) / tp.passes;
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // eight loads in flight
-    int64_t b = 0;
+    int32_t b = 0;
     for (; b + 8 <= G; b += 8)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u] += (double)part[(b + u) * cnt + i];
-    for (; b < G; ++b) acc[0] += (double)part[b * cnt + i];
+        for (int u = 0; u < 8; ++u) acc[u] += (double)q[(b + u) * step];
+    for (; b < G; ++b) acc[0] += (double)q[b * step];
     const double sum = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-    VT *d = dX + (i / KC) * lddx + i % KC;
+    VT *d = dX + (int64_t)(tp.row0(p) + j) * lddx + tp.first(p) + c;
     *d = (VT)(beta == 0.0 ? alpha * sum : alpha * sum + beta * (double)*d);
 }
 
@@ -2116,15 +2190,29 @@ hipError_t spmm_impl(const DevMat &a, int k, const VT *X, int64_t ldx, VT *Y, in
     });
 }
 
-// Columns of dX per pass of the LDS-privatised transpose (0: dX does not fit,
-// use global atomics): the widest of 8, 4, 2, 1 whose n x KC block fits in
-// LDS beside the tables, one 1024-thread workgroup per CU.
+// The LDS block of the transposed product: columns of A per block, padded to
+// a multiple of 32, and columns of dY a pass can hold (kMaxTransCols at
+// most).  Up to two column blocks (each decodes the streams again, against
+// scattered global atomics at 21 G lane operations a second); plane 0: dX
+// does not fit.
+constexpr int kMaxTransCols = 8;
+struct TransBlock {
+    int32_t blocks = 0, cols = 0, plane = 0, width = 0;
+};
 template <typename VT>
-int trans_lds_cols(const DevMat &a) {
-    const int64_t room = 160 * 1024 - 1024 - (int64_t)sizeof(Tables<VT>);
-    for (int c : {8, 4, 2, 1})
-        if ((a.n * c + a.n * c / 32 + 1) * (int64_t)sizeof(VT) <= room && a.n * c < (1ll << 31)) return c;
-    return 0;
+TransBlock trans_block(const DevMat &a) {
+    const int64_t room = (160 * 1024 - (int64_t)sizeof(Tables<VT>)) / (int64_t)sizeof(double);
+    TransBlock t;
+    for (int b = 1; b <= 2; ++b) {
+        const int64_t cols = (a.n + b - 1) / b, plane = (cols + 31) / 32 * 32;
+        if (plane == 0 || plane > room) continue;
+        t.blocks = b;
+        t.cols = (int32_t)cols;
+        t.plane = (int32_t)plane;
+        t.width = (int32_t)std::min<int64_t>(kMaxTransCols, room / plane);
+        break;
+    }
+    return t;
 }
 
 template <typename VT>
@@ -2132,35 +2220,56 @@ hipError_t spmm_t_impl(const DevMat &a, int k, const VT *dY, int64_t lddy, VT *d
                        double alpha, double beta, Launch L, void *work, size_t work_bytes,
                        hipStream_t st) {
     if (a.n == 0) return hipSuccess;
-    const int kcl = trans_lds_cols<VT>(a);
+    const TransBlock tb = trans_block<VT>(a);
     const int64_t G = L.num_cus;
-    if (kcl > 0 && a.nnz > 0 && a.num_waves > 0 &&
-        work_bytes >= (size_t)G * (size_t)a.n * (size_t)kcl * sizeof(VT)) {
+    if (tb.plane > 0 && a.nnz > 0 && a.num_waves > 0 &&
+        work_bytes >= (size_t)G * (size_t)tb.plane * (size_t)tb.width * sizeof(VT)) {
         VT *part = (VT *)work;
-        return for_kc(k, kcl, [&](auto KCc, int c0) {
-            constexpr int KC = decltype(KCc)::value;
-            if constexpr (KC > 8) {
-                return hipErrorInvalidValue;  // excluded by kcl
-            } else {
-                typename TransLdsSink<VT, KC>::Params sp;
-                sp.dY = dY + c0;
+        // passes of equal width; a launch runs at most kPasses of them side by
+        // side, each on its share of the CUs.  Workgroups past a quarter of
+        // the encoded waves (a pass of a small matrix) would only add copies
+        // to sum.
+        const int kPasses = (int)std::min<int64_t>(32, G);
+        const int chunks = (k + tb.width - 1) / tb.width;
+        TransPlan tp;
+        tp.n = a.n;
+        tp.k = k;
+        tp.width = (k + chunks - 1) / chunks;
+        tp.blocks = tb.blocks;
+        tp.cols = tb.cols;
+        tp.plane = tb.plane;
+        const int total = ((k + tp.width - 1) / tp.width) * tp.blocks;
+        const size_t dyn = (size_t)tp.width * tp.plane * sizeof(double);
+        for (tp.pass0 = 0; tp.pass0 < total; tp.pass0 += kPasses) {
+            tp.passes = std::min(kPasses, total - tp.pass0);
+            const int grid = (int)std::min<int64_t>(G, (int64_t)tp.passes * ((a.num_waves + 3) / 4));
+            auto run = [&](auto KCc) -> hipError_t {
+                constexpr int KC = decltype(KCc)::value;
+                typename TransLdsSink<VT, KC>::Params sp{};
+                sp.dY = dY;
                 sp.lddy = (uint32_t)lddy;
-                sp.lds = nullptr;
-                const size_t dyn = ((size_t)a.n * KC + (size_t)a.n * KC / 32 + 1) * sizeof(VT);
                 auto kern = a.layout == 1 ? pick_bd(a, trans_lds_kernel<1, VT, KC, 1>, trans_lds_kernel<1, VT, KC, 0>)
                                           : pick_bd(a, trans_lds_kernel<2, VT, KC, 1>, trans_lds_kernel<2, VT, KC, 0>);
                 hipError_t e = hipFuncSetAttribute((const void *)kern,
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
                 if (e != hipSuccess) return e;
-                hipLaunchKernelGGL(kern, dim3((unsigned)G), dim3(1024), dyn, st, a, sp, part);
-                e = hipGetLastError();
-                if (e != hipSuccess) return e;
-                const int64_t cnt = a.n * KC;
-                hipLaunchKernelGGL(trans_reduce_kernel<VT>, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0,
-                                   st, (const VT *)part, G, a.n, KC, dX + c0, lddx, alpha, beta);
+                hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1024), dyn, st, a, sp, tp, part);
                 return hipGetLastError();
-            }
-        });
+            };
+            hipError_t e = tp.width <= 1   ? run(std::integral_constant<int, 1>())
+                           : tp.width <= 2 ? run(std::integral_constant<int, 2>())
+                           : tp.width <= 3 ? run(std::integral_constant<int, 3>())
+                           : tp.width <= 4 ? run(std::integral_constant<int, 4>())
+                           : tp.width <= 6 ? run(std::integral_constant<int, 6>())
+                                           : run(std::integral_constant<int, 8>());
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(trans_reduce_kernel<VT>,
+                               dim3((unsigned)((tp.width * tp.plane + 255) / 256), (unsigned)tp.passes), dim3(256),
+                               0, st, (const VT *)part, tp, grid, dX, lddx, alpha, beta);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     }
     return for_kc(k, [&](auto KCc, int c0) {
         constexpr int KC = decltype(KCc)::value;
@@ -2267,8 +2376,8 @@ size_t spmm_scratch_bytes(const DevMat &a, int k) {
 }
 
 size_t spmm_t_work_bytes(const DevMat &a, bool f64, int num_cus) {
-    const int c = f64 ? trans_lds_cols<double>(a) : trans_lds_cols<float>(a);
-    return (size_t)num_cus * (size_t)a.n * (size_t)c * (f64 ? 8 : 4);
+    const TransBlock t = f64 ? trans_block<double>(a) : trans_block<float>(a);
+    return (size_t)num_cus * (size_t)t.plane * (size_t)t.width * (f64 ? 8 : 4);
 }
 
 hipError_t launch_spmm_t(const DevMat &a, bool f64, int k, const void *dY, int64_t lddy, void *dX,
