@@ -65,6 +65,7 @@ using gmut = __attribute__((address_space(1))) T *;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));                // 16-byte aligned
 typedef uint32_t u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));  // 16 bytes, 8-byte aligned
 typedef uint64_t u64_a4 __attribute__((aligned(4)));                        // 8 bytes, 4-byte aligned
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes, 4-byte aligned
 
 template <typename VT> struct Bits;
 template <> struct Bits<double> { typedef uint64_t T; };
@@ -781,7 +782,8 @@ struct TransLdsSink {
     __device__ __forceinline__ void finish_lane(int32_t, int, bool) {}
 };
 
-// decode to CSR: column and value bits of every nonzero
+// decode to CSR: column and value bits of every nonzero (streams with escapes
+// inside them; the others take decode_slice_csr)
 template <typename VT>
 struct DecodeSink {
     static constexpr bool kCoop = false;
@@ -807,6 +809,20 @@ struct DecodeSink {
     __device__ __forceinline__ void pre_step() {}
     __device__ __forceinline__ void finish_row(int32_t, int) {}
     __device__ __forceinline__ void finish_lane(int32_t, int, bool) {}
+};
+
+// Decode to CSR in two walks over a few segments at a time (decode_slice_csr):
+// not a sink of decode_slice, only its parameters.
+template <typename VT>
+struct CsrOut {
+    // waves per SIMD: the walks keep kBuf segments' words; more waves would
+    // not help a kernel bound by its stores
+    static constexpr int kOcc = 4;
+    struct Params {
+        int32_t *col;
+        typename Bits<VT>::T *vals;
+    };
+    static __device__ __forceinline__ uint32_t col_scale(const Params &) { return 1u; }
 };
 
 // --------------------------------------------------------- wave decoding
@@ -1283,6 +1299,173 @@ __device__ __forceinline__ void decode_slice(const DevMat &a, const Tables<VT> &
     }
 }
 
+// Decode encoded wave `slice` to CSR.  A lane's nonzeros are consecutive in
+// memory, but one segment is only 16 bytes of columns and 16 or 32 of values:
+// stored segment by segment, every cache line is written in pieces too far
+// apart in time for the L2 to put together (27-point stencil on 100^3, FP64:
+// 868 MB written for 317 MB of CSR, 0.27 ms).  So kBuf segments are decoded in
+// two walks: the first follows the stream's serial chain with the tables'
+// metadata alone and keeps each segment's three words; the second looks their
+// columns and values up and stores them, all within a short time (555 MB,
+// 0.18 ms: still bound by what the lines' pieces cost).  Escapes
+// stay in their regions until the second walk (in-stream escapes, whose
+// positions the first walk would need, take decode_slice with DecodeSink).
+template <int LAYOUT, typename VT, class Src, int TF>
+__device__ __forceinline__ void decode_slice_csr(const DevMat &a, const Tables<VT> &tb, int64_t slice, uint32_t lane,
+                                                 const typename CsrOut<VT>::Params &sp, Src &src, Cursor<VT> &cur,
+                                                 const LaneGeo &geo) {
+    constexpr int kBuf = 8;
+    typedef typename Bits<VT>::T BT;
+    const int64_t l = slice * kWave + lane;
+    const bool live = l < a.num_lanes;
+    const int64_t g0 = LAYOUT == 1 ? (int64_t)geo.row_beg : geo.g0;
+    const int cnt = LAYOUT == 1 ? (live ? geo.row_end - geo.row_beg : 0) : geo.cnt;
+    int32_t row = geo.row, row_end = geo.row_end, krow = geo.krow;
+    int2 n1 = geo.n1, n2 = geo.n2;
+    const int S = (cnt + 3) >> 2;
+    uint32_t pos = cur.pos, dpos = cur.dpos, vpos = cur.vpos;
+    uint32_t l1, l2, l3, x1 = 0, x2 = 0;
+    bool e1 = false, e2 = false;
+    {
+        const uint64_t mk = ballot(S > 0);
+        const uint32_t c = 4 * (uint32_t)__popcll(mk);
+        l1 = src.read(pos, mk);
+        l2 = src.read(pos + c, mk);
+        l3 = src.read(pos + 2 * c, mk);
+        pos += 3 * c;
+    }
+    const uint32_t pf = src.prefetch(pos, lane);
+    uint32_t d = 0, r = 1, col = first_base(a.first_mode, (uint32_t)row);
+    int64_t g = LAYOUT == 1 ? geo.gout : g0;
+    for (int j = 0; ballot(j < S) != 0; j += kBuf) {
+        uint32_t w1[kBuf], w2[kBuf], w3[kBuf];
+        // first walk: the words of segments j .. j + kBuf (see decode_slice
+        // for the steps; past a lane's end nothing of it is used)
+#pragma unroll
+        for (int i = 0; i < kBuf; ++i) {
+            w1[i] = e1 ? x1 : l1;
+            w2[i] = e2 ? x2 : l2;
+            w3[i] = l3;
+            const uint64_t m3 = ballot(j + i + 1 < S);  // lanes with a next segment
+            if (m3 == 0) continue;
+            uint32_t od[4], ov[4], md[4], mv[4];
+            slot_offsets<(int)sizeof(VEntry<VT>)>(w1[i], w2[i], w3[i], od, ov);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                md[k] = *(const uint32_t *)((const char *)tb.td + od[k] + 4);
+                mv[k] = ((const VEntry<VT> *)((const char *)tb.tv + ov[k]))->meta;
+                if constexpr (TF != 2) {
+                    md[k] &= ~kMetaEscape;
+                    mv[k] &= ~kMetaEscape;
+                }
+            }
+            uint32_t D, R;
+            if constexpr (TF >= 1) {
+                group_pairs(pair_rd(md[0], mv[0]), pair_rd(md[1], mv[1]), D, R);
+                e1 = append_word(d, r, D, R, x1);
+                group_pairs(pair_rd(md[2], mv[2]), pair_rd(md[3], mv[3]), D, R);
+                e2 = append_word(d, r, D, R, x2);
+            } else {
+                group_general(md[0], mv[0], md[1], mv[1], D, R);
+                e1 = append_and_check(d, r, D, R, x1);
+                group_general(md[2], mv[2], md[3], mv[3], D, R);
+                e2 = append_and_check(d, r, D, R, x2);
+            }
+            const uint64_t m1 = m3 & ~ballot(e1), m2 = m3 & ~ballot(e2);
+            const uint32_t c1 = 4 * (uint32_t)__popcll(m1), c2 = 4 * (uint32_t)__popcll(m2);
+            l1 = src.read(pos, m1);
+            l2 = src.read(pos + c1, m2);
+            l3 = src.read(pos + c1 + c2, m3);
+            pos += c1 + c2 + 4 * (uint32_t)__popcll(m3);
+        }
+        // second walk: columns and values
+#pragma unroll
+        for (int i = 0; i < kBuf; ++i) {
+            if (ballot(j + i < S) == 0) break;
+            const int nreal = min(max(cnt - 4 * (j + i), 0), 4);
+            uint32_t od[4], ov[4], dl[4], md[4], mv[4], cols[4];
+            VT v[4];
+            slot_offsets<(int)sizeof(VEntry<VT>)>(w1[i], w2[i], w3[i], od, ov);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint64_t e = *(const uint64_t *)((const char *)tb.td + od[k]);
+                const VEntry<VT> ve = *(const VEntry<VT> *)((const char *)tb.tv + ov[k]);
+                dl[k] = (uint32_t)e;
+                md[k] = (uint32_t)(e >> 32);
+                v[k] = ve.value();
+                mv[k] = ve.meta;
+            }
+            if constexpr (TF != 2) {
+                const uint32_t fl = md[0] | md[1] | md[2] | md[3] | mv[0] | mv[1] | mv[2] | mv[3];
+                if (ballot(nreal > 0) & ballot((int32_t)fl < 0)) {  // uniform
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const bool f = k < nreal && (int32_t)md[k] < 0;
+                        const uint64_t mk = ballot(f);
+                        if (f) dl[k] = ((gptr<uint32_t>)cur.ED)[dpos + lane_prefix(mk)];
+                        dpos += (uint32_t)__popcll(mk);
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const bool f = k < nreal && (int32_t)mv[k] < 0;
+                        const uint64_t mk = ballot(f);
+                        if (f) v[k] = ((gptr<VT>)cur.EV)[vpos + lane_prefix(mk)];
+                        vpos += (uint32_t)__popcll(mk);
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if constexpr (LAYOUT == 2) {
+                    if (k < nreal && g + k >= row_end) {  // the next nonempty row
+                        ++krow;
+                        row = n1.x;
+                        row_end = n1.y;
+                        n1 = n2;
+                        n2 = a.nzr[min((int64_t)krow + 2, a.n_nzr)];
+                        col = first_base(a.first_mode, (uint32_t)row);
+                    }
+                }
+                col += dl[k];
+                cols[k] = col;
+            }
+            if (nreal == 4) {
+                *(gmut<u32x4_a4>)(sp.col + g) = u32x4_a4{cols[0], cols[1], cols[2], cols[3]};
+                constexpr int per = 16 / (int)sizeof(VT);
+#pragma unroll
+                for (int h = 0; h < 4; h += per) {
+                    u32x4_a4 q;
+                    __builtin_memcpy(&q, v + h, 16);
+                    *(gmut<u32x4_a4>)(sp.vals + g + h) = q;
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if (k < nreal) {
+                        ((gmut<int32_t>)sp.col)[g + k] = (int32_t)cols[k];
+                        ((gmut<BT>)sp.vals)[g + k] = __builtin_bit_cast(BT, v[k]);
+                    }
+            }
+            g += 4;
+        }
+    }
+    src.retire(pf);
+    cur.pos = pos;
+    cur.dpos = dpos;
+    cur.vpos = vpos;
+}
+
+// the decoder of a sink (or of CsrOut)
+template <int LAYOUT, typename VT, class Sink, class Src, int TF>
+__device__ __forceinline__ void decode_wave(const DevMat &a, const Tables<VT> &tb, int64_t slice, uint32_t lane,
+                                            const typename Sink::Params &sp, Src &src, Cursor<VT> &cur,
+                                            const LaneGeo &geo) {
+    if constexpr (std::is_same<Sink, CsrOut<VT>>::value)
+        decode_slice_csr<LAYOUT, VT, Src, TF>(a, tb, slice, lane, sp, src, cur, geo);
+    else
+        decode_slice<LAYOUT, VT, Sink, Src, TF>(a, tb, slice, lane, sp, src, cur, geo);
+}
+
 // one encoded wave read straight from device memory
 template <int LAYOUT, typename VT, class Sink, int TF>
 __device__ __forceinline__ void decode_slice_global(const DevMat &a, const Tables<VT> &tb,
@@ -1293,7 +1476,7 @@ __device__ __forceinline__ void decode_slice_global(const DevMat &a, const Table
     Cursor<VT> cur{0, 0, 0, a.escd + uniform_load(a.doff + slice),
                    (const VT *)a.escv + uniform_load(a.voff + slice)};
     const LaneGeo geo = lane_geo<LAYOUT>(a, slice, lane, lane_first_row<LAYOUT>(a, slice, lane));
-    decode_slice<LAYOUT, VT, Sink, GlobalWords, TF>(a, tb, slice, lane, sp, src, cur, geo);
+    decode_wave<LAYOUT, VT, Sink, GlobalWords, TF>(a, tb, slice, lane, sp, src, cur, geo);
 }
 
 // Both tables into LDS in 16-byte pieces, every piece of a pass loaded before
@@ -1377,7 +1560,7 @@ __device__ __forceinline__ void decode_rows(const DevMat &a, Tables<VT> &tb,
         GlobalWords src{(const char *)(a.words + wo), 4 * (we - wo)};
         Cursor<VT> cur{0, 0, 0, a.escd + dof, (const VT *)a.escv + vof};
         set_progress_priority(share - k, share);
-        decode_slice<1, VT, Sink, GlobalWords, TF>(a, tb, s, lane, sp, src, cur, geo);
+        decode_wave<1, VT, Sink, GlobalWords, TF>(a, tb, s, lane, sp, src, cur, geo);
         geo = next;
         wo = wo1;
         we = we1;
@@ -2298,15 +2481,26 @@ hipError_t spmm_t_impl(const DevMat &a, int k, const VT *dY, int64_t lddy, VT *d
 template <typename VT>
 hipError_t decode_impl(const DevMat &a, int32_t *col, void *vals, Launch L, hipStream_t st) {
     if (a.nnz == 0 || a.num_waves == 0) return hipSuccess;
-    typename DecodeSink<VT>::Params sp;
-    sp.col = col;
-    sp.vals = (typename Bits<VT>::T *)vals;
-    typedef DecodeSink<VT> DS;
-    if (a.layout == 1)
-        return launch_persistent(pick_bd(a, decode_kernel<1, VT, DS, DS::kOcc, 1>, decode_kernel<1, VT, DS, DS::kOcc, 0>),
+    typedef typename Bits<VT>::T BT;
+    if (a.esc_in_stream && !a.no_escape) {
+        typedef DecodeSink<VT> DS;
+        const typename DS::Params sp{col, (BT *)vals};
+        if (a.layout == 1)
+            return launch_persistent(pick_bd(a, decode_kernel<1, VT, DS, DS::kOcc, 1>, decode_kernel<1, VT, DS, DS::kOcc, 0>),
+                                     a, L, st, a, sp);
+        return launch_persistent(pick_bd(a, decode_kernel<2, VT, DS, occ_nnz(DS::kOcc), 1>,
+                                         decode_kernel<2, VT, DS, occ_nnz(DS::kOcc), 0>),
                                  a, L, st, a, sp);
-    return launch_persistent(pick_bd(a, decode_kernel<2, VT, DS, occ_nnz(DS::kOcc), 1>,
-                                     decode_kernel<2, VT, DS, occ_nnz(DS::kOcc), 0>),
+    }
+    typedef CsrOut<VT> CO;
+    const typename CO::Params sp{col, (BT *)vals};
+    constexpr int occ = CO::kOcc;
+    if (a.layout == 1)
+        return launch_persistent(pick_tf(a, decode_kernel<1, VT, CO, occ, 2>, decode_kernel<1, VT, CO, occ, 1>,
+                                         decode_kernel<1, VT, CO, occ, 0>),
+                                 a, L, st, a, sp);
+    return launch_persistent(pick_tf(a, decode_kernel<2, VT, CO, occ, 2>, decode_kernel<2, VT, CO, occ, 1>,
+                                     decode_kernel<2, VT, CO, occ, 0>),
                              a, L, st, a, sp);
 }
 

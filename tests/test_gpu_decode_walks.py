@@ -1,0 +1,44 @@
+"""Decoding to CSR in two walks over eight segments (32 nonzeros of a lane) at
+a time: lane lengths around that edge, escapes of columns and values, rows
+that cross lanes and empty rows.  Columns and value bits are exact."""
+import numpy as np
+import pytest
+
+import paper_2603_01915_amd as P
+from gpu_common import need_gpu, progress
+
+pytestmark = pytest.mark.gpu
+
+
+def matrix(lens, n, dtype, escapes):
+    rng = np.random.default_rng(len(lens) + n)
+    rp = np.zeros(len(lens) + 1, np.int32)
+    rp[1:] = np.cumsum(lens)
+    step = n // 128  # a column drawn from each of L strips of the row
+    ci = np.concatenate([np.arange(L) * step + rng.integers(0, step, size=L) for L in lens]).astype(np.int32)
+    if escapes:  # more symbols than table slots: both alphabets escape
+        v = rng.standard_normal(len(ci)).astype(dtype)
+    else:
+        v = rng.choice([0.5, -1.5, 2.0], size=len(ci)).astype(dtype)
+    return rp, ci, v
+
+
+@pytest.mark.parametrize("layout,T", [("row", 0), ("nnz", 28), ("nnz", 32), ("nnz", 36), ("nnz", 100)])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("escapes", [False, True])
+@pytest.mark.parametrize("max_mult", [255, 256])
+def test_two_walks(layout, T, dtype, escapes, max_mult):
+    need_gpu()
+    n = 1 << 22 if escapes else 640
+    rng = np.random.default_rng(3)
+    for lens in ([0, 1, 2, 3, 4, 5, 27, 28, 29, 31, 32, 33, 34, 35, 36, 63, 64, 65, 100], [32] * 64, [33] * 65,
+                 list(rng.integers(0, 70, size=300))):
+        progress("decode walks %s T=%d %s %d rows" % (layout, T, dtype.__name__, len(lens)))
+        rp, ci, v = matrix(lens, n, dtype, escapes)
+        A = P.Matrix.from_csr(rp, ci, v, n, layout=layout, lane_nnz=T, max_mult=max_mult)
+        if escapes and len(ci) > 4500:
+            info = A.info()
+            assert info["esc_delta"] > 0 and info["esc_value"] > 0
+        r2, c2, v2 = A.decode_csr()
+        assert np.array_equal(r2.cpu().numpy(), rp) and np.array_equal(c2.cpu().numpy(), ci)
+        assert np.array_equal(v2.cpu().numpy().view(np.uint8), v.view(np.uint8))
