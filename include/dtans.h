@@ -273,9 +273,9 @@ dtans_status dtans_spmm_t(dtans_matrix *mat, int32_t k, const void *dY, int64_t 
  * strictly upper (or strictly lower) triangle S of a symmetric n x n matrix
  * A = S + S^T + diag(d); diag holds d (n values of the matrix's dtype,
  * device pointer; NULL for a zero diagonal).  Computes
- * y = alpha * (S x + S^T x + d .* x) + beta * y on `stream`: the product on
- * S (beta applied there), the diagonal term, then the transposed product on S
- * adding into y, so the summation order of the S^T part is not deterministic.
+ * y = alpha * (S x + S^T x + d .* x) + beta * y on `stream`: beta and the
+ * diagonal term first, then one decode of S whose nonzeros add to y twice, so
+ * the summation order is not deterministic.
  * x and y are n-vectors in device memory and must not overlap.  DTANS_EINVAL
  * for a non-square mat, null or aliased vectors; otherwise as dtans_spmv and
  * dtans_spmm_t.  mat must not contain diagonal entries (they would count twice).

@@ -17,8 +17,8 @@
 using namespace dtans;
 
 namespace dtans {
-// sym_kernels.hip: y[i] += alpha * d[i] * x[i]
-hipError_t launch_diag_axpy(bool f64, const void *d, const void *x, void *y, int64_t n, double alpha,
+// sym_kernels.hip: y[i] = beta * y[i] + alpha * d[i] * x[i] (d null: beta * y[i])
+hipError_t launch_sym_start(bool f64, const void *d, const void *x, void *y, int64_t n, double alpha, double beta,
                             hipStream_t st);
 }  // namespace dtans
 
@@ -859,14 +859,13 @@ dtans_status dtans_spmv_sym(dtans_matrix *mat, const void *diag, const void *x, 
     if (c.sigma) return set_err(DTANS_EUNSUPPORTED, "the symmetric product needs rows in CSR order");
     if (c.m > 0 && (!x || !y)) return set_err(DTANS_EINVAL, "null vector");
     if (x == y && c.m > 0) return set_err(DTANS_EINVAL, "y must not alias x");
-    // y = alpha S x + beta y, then y += alpha d .* x, then y += alpha S^T x
-    s = dtans_spmv(mat, x, y, alpha, beta, stream);
-    if (s) return s;
-    if (diag) {
-        hipError_t e = launch_diag_axpy(c.dtype == kF64, diag, x, y, c.m, alpha, st);
-        if (e != hipSuccess) return hip_err(e, "dtans_spmv_sym diagonal launch");
-    }
-    return dtans_spmm_t(mat, 1, x, 1, y, 1, alpha, 1.0, stream);
+    // y = beta y + alpha d .* x, then y += alpha (S + S^T) x
+    const bool f64 = c.dtype == kF64;
+    hipError_t e = launch_sym_start(f64, diag, x, y, c.m, alpha, beta, st);
+    if (e != hipSuccess) return hip_err(e, "dtans_spmv_sym start launch");
+    e = launch_sym(mat->view, f64, x, y, alpha, plan_launch(mat), st);
+    if (e != hipSuccess) return hip_err(e, "dtans_spmv_sym launch");
+    return DTANS_OK;
 }
 
 dtans_status dtans_decode_csr(dtans_matrix *mat, int32_t *row_ptr, int32_t *col_idx, void *vals,

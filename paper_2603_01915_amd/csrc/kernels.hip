@@ -782,6 +782,113 @@ struct TransLdsSink {
     __device__ __forceinline__ void finish_lane(int32_t, int, bool) {}
 };
 
+// A workgroup's sums for some of y, in LDS: 64 sets of 2 blocks, a block being
+// 64 consecutive elements (block b of y lives in set b mod 64).  A block is
+// claimed by the first element added to it; when both blocks of a set are
+// taken, elements go to y itself.  FP64 for either value type (the LDS adds
+// them nine times as fast as FP32, see TransLdsSink).
+struct BlockSums {
+    static constexpr uint32_t kSets = 64, kWays = 2, kBlock = 64, kFree = ~0u;
+    static constexpr size_t kBytes = kSets * kWays * (kBlock * sizeof(double) + sizeof(uint32_t));
+    double *sum;      // kSets * kWays * kBlock
+    uint32_t *owner;  // kSets * kWays: block numbers or kFree
+    __device__ __forceinline__ BlockSums(void *lds)
+        : sum((double *)lds), owner((uint32_t *)(sum + kSets * kWays * kBlock)) {}
+    // by the whole workgroup; a barrier has to follow
+    __device__ __forceinline__ void clear() const {
+        for (uint32_t i = threadIdx.x; i < kSets * kWays * kBlock; i += blockDim.x) sum[i] = 0.0;
+        for (uint32_t i = threadIdx.x; i < kSets * kWays; i += blockDim.x) owner[i] = kFree;
+    }
+    // the sum of element i, or null
+    __device__ __forceinline__ double *find(uint32_t i) const {
+        const uint32_t b = i / kBlock, set = b % kSets;
+        const uint2 t = *(const uint2 *)(owner + set * kWays);
+        int way = t.x == b ? 0 : (t.y == b ? 1 : -1);
+        if (way < 0) {
+            if (t.x == kFree) {
+                const uint32_t o = atomicCAS(owner + set * kWays, kFree, b);
+                if (o == kFree || o == b) way = 0;
+            }
+            if (way < 0 && t.y == kFree) {
+                const uint32_t o = atomicCAS(owner + set * kWays + 1, kFree, b);
+                if (o == kFree || o == b) way = 1;
+            }
+        }
+        return way < 0 ? nullptr : sum + (set * kWays + way) * kBlock + i % kBlock;
+    }
+    // y += alpha * sums; frees every block.  By the whole workgroup, between
+    // barriers.  (A sum of zero adds nothing.)
+    template <typename VT>
+    __device__ __forceinline__ void flush(VT *y, double alpha) const {
+        const uint32_t lane = threadIdx.x & (kWave - 1), nw = blockDim.x / kWave;
+        for (uint32_t s = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave); s < kSets * kWays; s += nw) {
+            const uint32_t b = owner[s];
+            if (b == kFree) continue;
+            const double v = sum[s * kBlock + lane];
+            if (v != 0.0) {
+                sum[s * kBlock + lane] = 0.0;
+                unsafeAtomicAdd(y + (uint64_t)b * kBlock + lane, (VT)(alpha * v));
+            }
+            if (lane == 0) owner[s] = kFree;
+        }
+    }
+};
+
+// y += alpha (S + S^T) x in one decode of S (the strict triangle of a
+// symmetric matrix): a nonzero (r, c, v) adds v x[c] to the sum of row r and
+// v x[r] to y[c], both through BlockSums.  Pieces of a row in several lanes
+// just add to the same element.
+template <typename VT>
+struct SymSink {
+    static constexpr bool kCoop = false;
+    static constexpr bool kPairs = false;
+    static constexpr int kOcc = 4;
+    struct Params {
+        const VT *x;
+        VT *y;
+        double alpha;
+        void *lds;  // set by the kernel
+    };
+    const Params p;
+    int32_t cur;  // row of acc (-1: none yet)
+    double xr, acc;
+    static __device__ __forceinline__ uint32_t col_scale(const Params &) { return 1u; }
+    __device__ SymSink(const Params &pp, int64_t, int32_t, bool) : p(pp), cur(-1), xr(0.0), acc(0.0) {}
+    __device__ __forceinline__ void add(uint32_t i, double v) const {
+        double *q = BlockSums(p.lds).find(i);
+        if (q) unsafeAtomicAdd(q, v);
+        else unsafeAtomicAdd(p.y + i, (VT)(p.alpha * v));
+    }
+    __device__ __forceinline__ void to_row(int32_t row) {
+        if (cur >= 0) add((uint32_t)cur, acc);
+        cur = row;
+        xr = (double)((gptr<VT>)p.x)[(uint32_t)row];
+        acc = 0.0;
+    }
+    template <bool MULTI>
+    __device__ __forceinline__ void segment(const uint32_t col[4], const VT v[4], int nreal, int64_t,
+                                            const int32_t rowk[4]) {
+        VT x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = ((gptr<VT>)p.x)[k < nreal ? col[k] : 0u];
+        if (!MULTI && nreal > 0 && cur < 0) to_row(rowk[0]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k < nreal) {
+                if (MULTI && rowk[k] != cur) to_row(rowk[k]);
+                add(col[k], (double)v[k] * xr);
+                acc = fma((double)v[k], (double)x[k], acc);
+            }
+    }
+    __device__ __forceinline__ void pre_step() {}
+    __device__ __forceinline__ void finish_row(int32_t, int) {
+        if (cur >= 0) add((uint32_t)cur, acc);
+    }
+    __device__ __forceinline__ void finish_lane(int32_t, int, bool) {
+        if (cur >= 0) add((uint32_t)cur, acc);
+    }
+};
+
 // decode to CSR: column and value bits of every nonzero (streams with escapes
 // inside them; the others take decode_slice_csr)
 template <typename VT>
@@ -1707,6 +1814,54 @@ __global__ __launch_bounds__(256) void trans_reduce_kernel(const VT *part, Trans
     *d = (VT)(beta == 0.0 ? alpha * sum : alpha * sum + beta * (double)*d);
 }
 
+// The symmetric product: each workgroup (one per CU) decodes one contiguous
+// run of encoded waves, a round of one wave per wavefront at a time, and adds
+// its sums to y after every kRounds rounds.  Global FP64 atomic adds bound
+// the product (182 G a second when coalesced), so neighbouring rows first
+// meet in LDS: on the 27-point stencil kRounds = 2 leaves about 2 of 14 adds
+// per row.  96^3, FP64: 37 us and 5 us to start y, against 111 us for the
+// product and the transposed product with global adds after each other; a
+// random graph (R-MAT scale 18), whose elements mostly find no block: 190
+// against 267 us.
+template <int LAYOUT, typename VT, int TF>
+__global__ __launch_bounds__(1024, 4) void sym_kernel(DevMat a, typename SymSink<VT>::Params sp) {
+    __shared__ __align__(16) Tables<VT> tb;
+    extern __shared__ __align__(16) unsigned char s_dyn[];
+    constexpr int kRounds = 2;
+    typename SymSink<VT>::Params q = sp;
+    q.lds = s_dyn;
+    const BlockSums sums(s_dyn);
+    sums.clear();  // (the barrier that ends the staging orders it)
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const int64_t wpb = blockDim.x / kWave;
+    // neighbouring runs on the same XCD, as in decode_sweep
+    const int64_t G = gridDim.x, xcd = blockIdx.x % kNumXcd, qq = G / kNumXcd, rr = G % kNumXcd;
+    const int64_t pos = xcd * qq + (xcd < rr ? xcd : rr) + blockIdx.x / kNumXcd;
+    const int64_t begin = pos * a.num_waves / G, end = (pos + 1) * a.num_waves / G;
+    const int64_t rounds = (end - begin + wpb - 1) / wpb;
+    int64_t s = begin + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    // row layout: the next wave's geometry and offsets are loaded while this
+    // one decodes (see decode_rows)
+    auto clamp = [&](int64_t i) { return i < end ? i : (end > begin ? end - 1 : (int64_t)0); };
+    LaneGeo geo = lane_geo<LAYOUT>(a, clamp(s), lane, lane_first_row<LAYOUT>(a, clamp(s), lane));
+    stage_tables<VT>(a, tb, 1u);
+    for (int64_t i = 0; i < rounds; ++i, s += wpb) {
+        if (s < end) {
+            const LaneGeo next = lane_geo<LAYOUT>(a, clamp(s + wpb), lane, lane_first_row<LAYOUT>(a, clamp(s + wpb), lane));
+            const uint64_t wo = uniform_load(a.woff + s), we = uniform_load(a.woff + s + 1);
+            GlobalWords src{(const char *)(a.words + wo), 4 * (we - wo)};
+            Cursor<VT> cur{0, 0, 0, a.escd + uniform_load(a.doff + s), (const VT *)a.escv + uniform_load(a.voff + s)};
+            decode_slice<LAYOUT, VT, SymSink<VT>, GlobalWords, TF>(a, tb, s, lane, q, src, cur, geo);
+            geo = next;
+        }
+        if (i % kRounds == kRounds - 1 || i == rounds - 1) {  // uniform over the workgroup
+            __syncthreads();
+            sums.flush(q.y, q.alpha);
+            __syncthreads();
+        }
+    }
+}
+
 // Same work as decode_kernel, with every wavefront owning one contiguous run
 // of encoded waves (so that its streams are adjacent in memory) and reading
 // them through an LDS ring (RingWords).  The XCD shares are those of
@@ -2479,6 +2634,22 @@ hipError_t spmm_t_impl(const DevMat &a, int k, const VT *dY, int64_t lddy, VT *d
 }
 
 template <typename VT>
+hipError_t sym_impl(const DevMat &a, const VT *x, VT *y, double alpha, Launch L, hipStream_t st) {
+    if (a.nnz == 0 || a.num_waves == 0) return hipSuccess;
+    const typename SymSink<VT>::Params sp{x, y, alpha, nullptr};
+    auto kern = a.layout == 1 ? pick_tf(a, sym_kernel<1, VT, 2>, sym_kernel<1, VT, 1>, sym_kernel<1, VT, 0>)
+                              : pick_tf(a, sym_kernel<2, VT, 2>, sym_kernel<2, VT, 1>, sym_kernel<2, VT, 0>);
+    hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)BlockSums::kBytes);
+    if (e != hipSuccess) return e;
+    // small matrices: four waves a workgroup at least, so that fewer tables
+    // are staged
+    const int64_t grid = std::min<int64_t>(L.num_cus, (a.num_waves + 3) / 4);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1024), BlockSums::kBytes, st, a, sp);
+    return hipGetLastError();
+}
+
+template <typename VT>
 hipError_t decode_impl(const DevMat &a, int32_t *col, void *vals, Launch L, hipStream_t st) {
     if (a.nnz == 0 || a.num_waves == 0) return hipSuccess;
     typedef typename Bits<VT>::T BT;
@@ -2582,6 +2753,11 @@ hipError_t launch_spmm_t(const DevMat &a, bool f64, int k, const void *dY, int64
                                    L, work, work_bytes, st);
     return spmm_t_impl<float>(a, k, (const float *)dY, lddy, (float *)dX, lddx, alpha, beta, L,
                               work, work_bytes, st);
+}
+
+hipError_t launch_sym(const DevMat &a, bool f64, const void *x, void *y, double alpha, Launch L, hipStream_t st) {
+    return f64 ? sym_impl<double>(a, (const double *)x, (double *)y, alpha, L, st)
+               : sym_impl<float>(a, (const float *)x, (float *)y, alpha, L, st);
 }
 
 hipError_t launch_decode(const DevMat &a, bool f64, int32_t *col, void *vals, Launch L,
