@@ -154,16 +154,15 @@ struct SpmmSink {
         uint32_t pair_x = 0;
     };
     const Params p;
-    int64_t lane;
+    uint32_t lane;
     int32_t cur, head_row;  // row being accumulated; the lane's head row or -1
     ACC acc[KC];
     VT pv[DEFER ? 4 : 1], px[DEFER ? 4 : 1][KC];  // deferred segment
     int32_t prow[DEFER == 2 ? 4 : 1];             // its rows (DEFER 2)
     int pn;                                       // its nonzeros (0: none)
-    // cur starts at -1: a row is finished only after the sink has seen one of
-    // its nonzeros
+    // cur starts at the lane's first row, which holds its first nonzero
     __device__ SpmmSink(const Params &pp, int64_t l, int32_t first_row, bool first_is_head)
-        : p(pp), lane(l), cur(-1), head_row(first_is_head ? first_row : -1), pn(0) {
+        : p(pp), lane((uint32_t)l), cur(first_row), head_row(first_is_head ? first_row : -1), pn(0) {
 #pragma unroll
         for (int c = 0; c < KC; ++c) acc[c] = (ACC)0;
     }
@@ -197,7 +196,7 @@ struct SpmmSink {
                 for (int k = 0; k < 4; ++k)
                     if (k < pn) {
                         if (prow[k] != cur) {
-                            if (cur >= 0) store(cur, cur == head_row ? kHead : kComplete);
+                            store(cur, cur == head_row ? kHead : kComplete);
                             cur = prow[k];
                         }
 #pragma unroll
@@ -225,7 +224,7 @@ struct SpmmSink {
                 y[c] = (VT)(p.beta == 0.0 ? p.alpha * (double)acc[c]
                                           : p.alpha * (double)acc[c] + p.beta * (double)y[c]);
         } else {
-            double *q = p.partial + (2 * lane + (kind == kTail ? 1 : 0)) * KC;
+            double *q = p.partial + (2 * (int64_t)lane + (kind == kTail ? 1 : 0)) * KC;
 #pragma unroll
             for (int c = 0; c < KC; ++c) q[c] = (double)acc[c];
         }
@@ -392,16 +391,19 @@ struct SpmmSink {
                     }
                 return;
             }
+            // (every lane loads, column 0 past its end: the loads stay
+            // together, with no branch between them)
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k < nreal)
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t cc = k < nreal ? col[k] : 0u;
 #pragma unroll
-                    for (int c = 0; c < KC; ++c) x[k][c] = xrow(col[k])[c];
+                for (int c = 0; c < KC; ++c) x[k][c] = xrow(cc)[c];
+            }
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 if (k < nreal) {
                     if (MULTI && rowk[k] != cur) {
-                        if (cur >= 0) store(cur, cur == head_row ? kHead : kComplete);
+                        store(cur, cur == head_row ? kHead : kComplete);
                         cur = rowk[k];
                     }
 #pragma unroll
@@ -424,7 +426,7 @@ struct SpmmSink {
                 }
                 if (k < nreal) {
                     if (MULTI && rowk[k] != cur) {
-                        if (cur >= 0) store(cur, cur == head_row ? kHead : kComplete);
+                        store(cur, cur == head_row ? kHead : kComplete);
                         cur = rowk[k];
                     }
 #pragma unroll
@@ -445,7 +447,7 @@ struct SpmmSink {
     // one partial per wavefront a row spans instead of one per lane.
     __device__ __forceinline__ void finish_lane(int32_t row, int kind, bool live) {
         consume();
-        const uint32_t wl = (uint32_t)lane & (kWave - 1);
+        const uint32_t wl = lane & (kWave - 1);
         const bool mid = live && kind == kMid;
         const int32_t key = mid ? row : -1;
 #pragma unroll
@@ -519,9 +521,9 @@ struct CoopSpmmSink {
     uint32_t grp, part;      // group, column chunk of this lane
     int64_t wave0;           // global index of stream 0 of the wave
     ACC acc[G][CL];
-    int32_t cur[G];          // row being summed in slot i (-1 before the first nonzero)
+    int32_t cur[G];          // row being summed in slot i (at first the stream's first row)
     int32_t head_row[G];     // the slot's first row when it began before the stream, else -1
-    int32_t last;            // row of this lane's last nonzero so far (-1 before the first)
+    int32_t last;            // row of this lane's last nonzero so far (at first its first row)
 
     static __device__ __forceinline__ uint32_t col_scale(const Params &pp) {
         return pp.ldx * (uint32_t)sizeof(VT);
@@ -531,12 +533,12 @@ struct CoopSpmmSink {
         grp = lane / G;
         part = lane % G;
         wave0 = l - lane;
-        last = -1;
+        last = first_row;
         const int32_t hr = first_is_head ? first_row : -1;
 #pragma unroll
         for (int i = 0; i < G; ++i) {
             const uint32_t src = grp * G + i;
-            cur[i] = -1;
+            cur[i] = (int32_t)lane_value((uint32_t)first_row, src);
             head_row[i] = (int32_t)lane_value((uint32_t)hr, src);
 #pragma unroll
             for (int c = 0; c < CL; ++c) acc[i][c] = (ACC)0;
@@ -602,7 +604,7 @@ struct CoopSpmmSink {
             if (r + kAhead < R) fetch(r + kAhead);
             if (j < nr[i]) {
                 if (MULTI && moved && rr != cur[i]) {
-                    if (cur[i] >= 0) store(i, cur[i], cur[i] == head_row[i] ? kHead : kComplete);
+                    store(i, cur[i], cur[i] == head_row[i] ? kHead : kComplete);
                     cur[i] = rr;
                 }
 #pragma unroll
@@ -1086,7 +1088,21 @@ struct Cursor {
     uint32_t pos, dpos, vpos;
     const uint32_t *ED;
     const VT *EV;
+    // elements of the wave's escape regions to bring into L2 when it starts
+    // (0: none)
+    uint32_t nd = 0, nv = 0;
 };
+
+// As GlobalWords::prefetch for the escape regions: one load per lane touches
+// the first 64 cache lines of each, which would otherwise come from memory in
+// the middle of the steps that use them.
+template <typename VT>
+__device__ __forceinline__ uint32_t prefetch_escapes(const Cursor<VT> &c, uint32_t lane) {
+    uint32_t t = 0;
+    if (c.nd) t = ((gptr<uint32_t>)c.ED)[min(32 * lane, c.nd - 1)];  // uniform
+    if (c.nv) t ^= ((gptr<uint32_t>)c.EV)[min(32 * lane, (uint32_t)(sizeof(VT) / 4) * c.nv - 1)];
+    return t;
+}
 
 // Where a lane's stream sits in the matrix: its first nonzero g0 and count
 // (the row layout keeps only the row's [beg, end)); the row of that nonzero
@@ -1094,33 +1110,44 @@ struct Cursor {
 // walks the list of nonempty rows ({row, end} pairs, a sentinel {m, nnz} at
 // the end), so a lane never visits empty rows (their y is written by
 // empty_rows_kernel) and crosses exactly one row per nonzero that starts one;
-// it keeps the next two list entries loaded ahead (n1, n2).  Finding the
-// first entry takes two dependent loads (lane_row, then the list), so
-// callers may issue the first a wave ahead (lane_first_row).
+// it keeps the next four list entries, all that one segment can cross
+// (next_rows).  Finding the first entry takes two dependent loads (lane_row,
+// then the list), so callers issue the first a wave ahead (lane_first_row).
 struct LaneGeo {
-    int64_t g0;
+    int32_t g0;
     int cnt;
     int32_t krow;  // layout NNZ: index of `row` in the nonempty-row list
     int32_t row, row_beg, row_end;
-    int2 n1, n2;
+    int2 next[4];  // layout NNZ: the entries after krow
     // layout ROW: the row of the original matrix this lane's row is (rows
     // sorted within windows are encoded in that order) and the position of
     // its first nonzero there
     int32_t orow;
-    int64_t gout;
+    int32_t gout;
 };
 
 template <int LAYOUT>
 __device__ __forceinline__ int32_t lane_first_row(const DevMat &a, int64_t slice, uint32_t lane) {
     const int64_t l = slice * kWave + lane;
-    if (l >= a.num_lanes) return 0;
-    return LAYOUT == 1 ? (int32_t)l : a.lane_row[l];
+    if constexpr (LAYOUT == 1) return l < a.num_lanes ? (int32_t)l : 0;
+    else return ((gptr<int32_t>)a.lane_row)[l < a.num_lanes ? l : 0];
+}
+
+// The list entries krow + 1 .. krow + 4.  Entries past the sentinel lie in the
+// buffer's padding; no nonzero reaches them.
+__device__ __forceinline__ void next_rows(const DevMat &a, int32_t krow, int2 next[4]) {
+    const gptr<u32x4_a8> q = (gptr<u32x4_a8>)(a.nzr + (int64_t)krow + 1);
+    const u32x4_a8 lo = q[0], hi = q[1];
+    next[0] = make_int2((int)lo.x, (int)lo.y);
+    next[1] = make_int2((int)lo.z, (int)lo.w);
+    next[2] = make_int2((int)hi.x, (int)hi.y);
+    next[3] = make_int2((int)hi.z, (int)hi.w);
 }
 
 template <int LAYOUT>
 __device__ __forceinline__ LaneGeo lane_geo(const DevMat &a, int64_t slice, uint32_t lane,
                                             int32_t first) {
-    LaneGeo q{0, 0, 0, 0, 0, 0, make_int2(0, 0), make_int2(0, 0), 0, 0};
+    LaneGeo q;
     const int64_t l = slice * kWave + lane;
     if constexpr (LAYOUT == 1) {
         // the row's bounds only (lanes past the last row read the last
@@ -1136,18 +1163,58 @@ __device__ __forceinline__ LaneGeo lane_geo(const DevMat &a, int64_t slice, uint
             q.orow = ((gptr<int32_t>)a.row_perm)[lc];
             q.gout = ((gptr<int32_t>)a.orig_row_ptr)[q.orow];
         }
-    } else if (l < a.num_lanes) {
-        q.g0 = l * (int64_t)a.lane_nnz;
-        q.cnt = (int)min((int64_t)a.lane_nnz, a.nnz - q.g0);
+    } else {
+        // (lanes past the last one read lane 0's row and hold no nonzeros)
+        const bool live = l < a.num_lanes;
+        q.g0 = live ? (int32_t)(l * a.lane_nnz) : 0;
+        q.cnt = live ? min(a.lane_nnz, (int32_t)a.nnz - q.g0) : 0;
         q.krow = first;
         const int2 c = a.nzr[first];
         q.row = c.x;
         q.row_end = c.y;
         q.row_beg = first > 0 ? a.nzr[first - 1].y : 0;
-        q.n1 = a.nzr[min((int64_t)first + 1, a.n_nzr)];
-        q.n2 = a.nzr[min((int64_t)first + 2, a.n_nzr)];
+        next_rows(a, first, q.next);
     }
     return q;
+}
+
+// Layout NNZ: the rows of one segment, nonzeros g .. g + nreal: a nonzero at
+// the end of the current row starts the next nonempty one, where the column
+// restarts.  Selects over the four entries at hand, with no load in the chain
+// from one nonzero to the next; the entries after the new row are requested
+// at the end, for the next segment that crosses one.  (The entries were
+// loaded two crossings ahead, one load per crossing, under a branch per
+// nonzero: a segment in which several lanes crossed rows at different
+// nonzeros waited for memory at each of them.)  cols: deltas in, columns out.
+__device__ __forceinline__ void cross_rows(const DevMat &a, uint32_t scale, uint32_t g, int nreal, int32_t &row,
+                                           int32_t &row_end, int32_t &krow, int2 next[4], bool &head, uint32_t &col,
+                                           uint32_t cols[4], int32_t rowk[4]) {
+    if (!ballot(nreal > 0 && g + (uint32_t)nreal > (uint32_t)row_end)) {  // uniform: no lane crosses a row
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            col += cols[k];
+            cols[k] = col;
+            rowk[k] = row;
+        }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const bool c = k < nreal && g + (uint32_t)k >= (uint32_t)row_end;
+        row = c ? next[0].x : row;
+        row_end = c ? next[0].y : row_end;
+#pragma unroll
+        for (int i = 0; i + k < 3; ++i) {
+            next[i].x = c ? next[i + 1].x : next[i].x;
+            next[i].y = c ? next[i + 1].y : next[i].y;
+        }
+        krow += c ? 1 : 0;
+        head = head && !c;
+        col = (c ? first_base(a.first_mode, (uint32_t)row) * scale : col) + cols[k];
+        cols[k] = col;
+        rowk[k] = row;
+    }
+    next_rows(a, krow, next);
 }
 
 // LDS byte offsets of a segment's eight slots (unpack8 of dtans_core.hpp
@@ -1167,6 +1234,40 @@ __device__ __forceinline__ void slot_offsets(uint32_t w1, uint32_t w2, uint32_t 
     ov[3] = (w1 >> 20) * E;                                        // i8 = w1[20:32]
 }
 
+// A segment's escaped deltas and values from their regions, in the order
+// (nonzero, lane): flag bits in md and mv, nreal nonzeros in this lane.  All
+// eight loads are issued before any of their values is used (a use between
+// them made the wavefront wait for memory up to eight times a segment); lanes
+// without an escape read the region's next element, or, past the last one,
+// the buffer's padding.
+template <typename VT>
+__device__ __forceinline__ void take_escapes(gptr<uint32_t> ED, gptr<VT> EV, uint32_t &dpos, uint32_t &vpos, int nreal,
+                                             const uint32_t md[4], const uint32_t mv[4], uint32_t scale,
+                                             uint32_t dl[4], VT v[4]) {
+    uint32_t rd[4];
+    VT rv[4];
+    // (uniform branches: in most matrices few of the eight hold an escape)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const bool f = k < nreal && (int32_t)md[k] < 0;
+        const uint64_t mk = ballot(f);
+        if (mk) rd[k] = ED[dpos + (f ? lane_prefix(mk) : 0u)];
+        dpos += (uint32_t)__popcll(mk);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const bool f = k < nreal && (int32_t)mv[k] < 0;
+        const uint64_t mk = ballot(f);
+        if (mk) rv[k] = EV[vpos + (f ? lane_prefix(mk) : 0u)];
+        vpos += (uint32_t)__popcll(mk);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (k < nreal && (int32_t)md[k] < 0) dl[k] = rd[k] * scale;
+        if (k < nreal && (int32_t)mv[k] < 0) v[k] = rv[k];
+    }
+}
+
 // Decode encoded wave `slice` (lanes slice*64 .. slice*64+63) and feed the
 // nonzeros of this thread's lane to a sink constructed here.
 // TF, the table format: 0 some base is 256 (the paper's M; a digit group's
@@ -1182,15 +1283,20 @@ __device__ __forceinline__ void decode_slice(const DevMat &a, const Tables<VT> &
                                              Src &src, Cursor<VT> &cur, const LaneGeo &geo) {
     const int64_t l = slice * kWave + lane;
     const bool live = l < a.num_lanes;
-    const int64_t g0 = LAYOUT == 1 ? (int64_t)geo.row_beg : geo.g0;
+    const int32_t g0 = LAYOUT == 1 ? geo.row_beg : geo.g0;
     const int cnt = LAYOUT == 1 ? (live ? geo.row_end - geo.row_beg : 0) : geo.cnt;
-    int32_t row = geo.row, row_beg = geo.row_beg, row_end = geo.row_end, krow = geo.krow;
-    int2 n1 = geo.n1, n2 = geo.n2;
+    int32_t row = geo.row, row_end = geo.row_end, krow = geo.krow;
+    bool head = LAYOUT == 2 && geo.row_beg < g0;  // the current row began in an earlier lane
+    int2 next[4];
+    if constexpr (LAYOUT == 2) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) next[i] = geo.next[i];
+    }
     // the sink sees rows and nonzero positions of the original matrix (row
     // layout: rows may be encoded in another order); the decoder's own row
     // (first deltas) is the encoded one
     const int32_t srow = LAYOUT == 1 ? geo.orow : row;
-    Sink sink(sp, l, srow, LAYOUT == 2 && row_beg < g0);
+    Sink sink(sp, l, srow, head);
     const uint32_t scale = Sink::col_scale(sp);  // column deltas arrive multiplied by it
     const int S = (cnt + 3) >> 2;
     const int F = min(S - 1, cnt >> 2);  // steps j < F: four nonzeros and a next segment
@@ -1218,8 +1324,18 @@ __device__ __forceinline__ void decode_slice(const DevMat &a, const Tables<VT> &
         src.consumed(pos);
     }
     const uint32_t pf = src.prefetch(pos, lane);
+    const uint32_t pe = TF != 2 ? prefetch_escapes<VT>(cur, lane) : 0u;
+    if constexpr (LAYOUT == 2) {
+        // The lane's rows are waited for here, behind the requests for the
+        // first words: loaded on some paths only, they would otherwise be
+        // waited for in every step of the loops below, and with them whatever
+        // was requested after them.
+        asm volatile("" : "+v"(row), "+v"(row_end));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(next[i].x), "+v"(next[i].y));
+    }
     uint32_t d = 0, r = 1, col = first_base(a.first_mode, (uint32_t)row) * scale;
-    int64_t g = LAYOUT == 1 ? geo.gout : g0;
+    uint32_t g = (uint32_t)(LAYOUT == 1 ? geo.gout : g0);
 
     auto step = [&](auto fullc, int j) {
         constexpr bool FULL = decltype(fullc)::value;
@@ -1276,20 +1392,8 @@ __device__ __forceinline__ void decode_slice(const DevMat &a, const Tables<VT> &
                         pos += (uint32_t)sizeof(VT) * (uint32_t)__popcll(mk);
                     }
                 } else {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const bool f = act && k < rem && (int32_t)md[k] < 0;
-                        const uint64_t mk = ballot(f);
-                        if (f) dl[k] = ((gptr<uint32_t>)ED)[dpos + lane_prefix(mk)] * scale;
-                        dpos += (uint32_t)__popcll(mk);
-                    }
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const bool f = act && k < rem && (int32_t)mv[k] < 0;
-                        const uint64_t mk = ballot(f);
-                        if (f) v[k] = ((gptr<VT>)EV)[vpos + lane_prefix(mk)];
-                        vpos += (uint32_t)__popcll(mk);
-                    }
+                    take_escapes<VT>((gptr<uint32_t>)ED, (gptr<VT>)EV, dpos, vpos, act ? min(rem, 4) : 0, md, mv,
+                                     scale, dl, v);
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
@@ -1357,23 +1461,10 @@ __device__ __forceinline__ void decode_slice(const DevMat &a, const Tables<VT> &
             else sink.template segment<false>(cols, v, nreal, g, rowk);
         } else {
             // resolve row boundaries first: a column delta restarts at every
-            // row; a nonzero at the end of the current row starts the next
-            // nonempty one, whose predecessor the sink finishes
+            // row; the sink finishes the rows left behind
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (k < nreal && g + k >= row_end) {
-                    ++krow;
-                    row_beg = row_end;
-                    row = n1.x;
-                    row_end = n1.y;
-                    n1 = n2;
-                    n2 = a.nzr[min((int64_t)krow + 2, a.n_nzr)];
-                    col = first_base(a.first_mode, (uint32_t)row) * scale;
-                }
-                col += dl[k];
-                cols[k] = col;
-                rowk[k] = row;
-            }
+            for (int k = 0; k < 4; ++k) cols[k] = dl[k];
+            cross_rows(a, scale, g, nreal, row, row_end, krow, next, head, col, cols, rowk);
             sink.template segment<true>(cols, v, nreal, g, rowk);
         }
         g += 4;
@@ -1389,6 +1480,7 @@ __device__ __forceinline__ void decode_slice(const DevMat &a, const Tables<VT> &
     }
     for (; ballot(j < S) != 0; ++j) step(std::false_type(), j);
     src.retire(pf);
+    if (TF != 2) src.retire(pe);
     cur.pos = pos;
     cur.dpos = dpos;
     cur.vpos = vpos;
@@ -1400,9 +1492,8 @@ __device__ __forceinline__ void decode_slice(const DevMat &a, const Tables<VT> &
         // `row` holds this lane's last nonzeros: complete when it ends here;
         // started in an earlier lane, a head when it ends here, else a
         // middle; else a tail
-        const int64_t gend = g0 + cnt;
-        const bool ends = row_end <= gend;
-        sink.finish_lane(row, row_beg < g0 ? (ends ? kHead : kMid) : (ends ? kComplete : kTail), live);
+        const bool ends = row_end <= g0 + cnt;
+        sink.finish_lane(row, head ? (ends ? kHead : kMid) : (ends ? kComplete : kTail), live);
     }
 }
 
@@ -1425,10 +1516,14 @@ __device__ __forceinline__ void decode_slice_csr(const DevMat &a, const Tables<V
     typedef typename Bits<VT>::T BT;
     const int64_t l = slice * kWave + lane;
     const bool live = l < a.num_lanes;
-    const int64_t g0 = LAYOUT == 1 ? (int64_t)geo.row_beg : geo.g0;
     const int cnt = LAYOUT == 1 ? (live ? geo.row_end - geo.row_beg : 0) : geo.cnt;
     int32_t row = geo.row, row_end = geo.row_end, krow = geo.krow;
-    int2 n1 = geo.n1, n2 = geo.n2;
+    bool head = false;
+    int2 next[4];
+    if constexpr (LAYOUT == 2) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) next[i] = geo.next[i];
+    }
     const int S = (cnt + 3) >> 2;
     uint32_t pos = cur.pos, dpos = cur.dpos, vpos = cur.vpos;
     uint32_t l1, l2, l3, x1 = 0, x2 = 0;
@@ -1443,7 +1538,7 @@ __device__ __forceinline__ void decode_slice_csr(const DevMat &a, const Tables<V
     }
     const uint32_t pf = src.prefetch(pos, lane);
     uint32_t d = 0, r = 1, col = first_base(a.first_mode, (uint32_t)row);
-    int64_t g = LAYOUT == 1 ? geo.gout : g0;
+    int64_t g = LAYOUT == 1 ? geo.gout : geo.g0;
     for (int j = 0; ballot(j < S) != 0; j += kBuf) {
         uint32_t w1[kBuf], w2[kBuf], w3[kBuf];
         // first walk: the words of segments j .. j + kBuf (see decode_slice
@@ -1505,36 +1600,20 @@ __device__ __forceinline__ void decode_slice_csr(const DevMat &a, const Tables<V
             if constexpr (TF != 2) {
                 const uint32_t fl = md[0] | md[1] | md[2] | md[3] | mv[0] | mv[1] | mv[2] | mv[3];
                 if (ballot(nreal > 0) & ballot((int32_t)fl < 0)) {  // uniform
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const bool f = k < nreal && (int32_t)md[k] < 0;
-                        const uint64_t mk = ballot(f);
-                        if (f) dl[k] = ((gptr<uint32_t>)cur.ED)[dpos + lane_prefix(mk)];
-                        dpos += (uint32_t)__popcll(mk);
-                    }
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const bool f = k < nreal && (int32_t)mv[k] < 0;
-                        const uint64_t mk = ballot(f);
-                        if (f) v[k] = ((gptr<VT>)cur.EV)[vpos + lane_prefix(mk)];
-                        vpos += (uint32_t)__popcll(mk);
-                    }
+                    take_escapes<VT>((gptr<uint32_t>)cur.ED, (gptr<VT>)cur.EV, dpos, vpos, nreal, md, mv, 1u, dl, v);
                 }
             }
+            if constexpr (LAYOUT == 2) {
+                int32_t rowk[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if constexpr (LAYOUT == 2) {
-                    if (k < nreal && g + k >= row_end) {  // the next nonempty row
-                        ++krow;
-                        row = n1.x;
-                        row_end = n1.y;
-                        n1 = n2;
-                        n2 = a.nzr[min((int64_t)krow + 2, a.n_nzr)];
-                        col = first_base(a.first_mode, (uint32_t)row);
-                    }
+                for (int k = 0; k < 4; ++k) cols[k] = dl[k];
+                cross_rows(a, 1u, (uint32_t)g, nreal, row, row_end, krow, next, head, col, cols, rowk);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    col += dl[k];
+                    cols[k] = col;
                 }
-                col += dl[k];
-                cols[k] = col;
             }
             if (nreal == 4) {
                 *(gmut<u32x4_a4>)(sp.col + g) = u32x4_a4{cols[0], cols[1], cols[2], cols[3]};
@@ -1573,18 +1652,34 @@ __device__ __forceinline__ void decode_wave(const DevMat &a, const Tables<VT> &t
         decode_slice<LAYOUT, VT, Sink, Src, TF>(a, tb, slice, lane, sp, src, cur, geo);
 }
 
-// one encoded wave read straight from device memory
-template <int LAYOUT, typename VT, class Sink, int TF>
-__device__ __forceinline__ void decode_slice_global(const DevMat &a, const Tables<VT> &tb,
-                                                    int64_t slice, uint32_t lane,
-                                                    const typename Sink::Params &sp) {
-    const uint64_t wo = uniform_load(a.woff + slice), we = uniform_load(a.woff + slice + 1);
-    GlobalWords src{(const char *)(a.words + wo), 4 * (we - wo)};
-    Cursor<VT> cur{0, 0, 0, a.escd + uniform_load(a.doff + slice),
-                   (const VT *)a.escv + uniform_load(a.voff + slice)};
-    const LaneGeo geo = lane_geo<LAYOUT>(a, slice, lane, lane_first_row<LAYOUT>(a, slice, lane));
-    decode_wave<LAYOUT, VT, Sink, GlobalWords, TF>(a, tb, slice, lane, sp, src, cur, geo);
-}
+// Offsets of an encoded wave's words and escapes (uniform, scalar loads).  ESC:
+// with the ends of the escape regions, for their prefetch (nonzero layout; in
+// the row layout's kernels, at eight waves per SIMD, the scalars that hold
+// them would spill).
+template <bool ESC>
+struct WaveSpan {
+    uint64_t w0, w1, d0, v0, d1 = 0, v1 = 0;
+    __device__ __forceinline__ WaveSpan(const DevMat &a, int64_t s)
+        : w0(uniform_load(a.woff + s)), w1(uniform_load(a.woff + s + 1)), d0(uniform_load(a.doff + s)),
+          v0(uniform_load(a.voff + s)) {
+        if constexpr (ESC) {
+            d1 = uniform_load(a.doff + s + 1);
+            v1 = uniform_load(a.voff + s + 1);
+        }
+    }
+    __device__ __forceinline__ GlobalWords words(const DevMat &a) const {
+        return GlobalWords{(const char *)(a.words + w0), 4 * (w1 - w0)};
+    }
+    template <typename VT>
+    __device__ __forceinline__ Cursor<VT> cursor(const DevMat &a) const {
+        Cursor<VT> c{0, 0, 0, a.escd + d0, (const VT *)a.escv + v0, 0, 0};
+        if constexpr (ESC) {
+            c.nd = (uint32_t)(d1 - d0);
+            c.nv = (uint32_t)(v1 - v0);
+        }
+        return c;
+    }
+};
 
 // Both tables into LDS in 16-byte pieces, every piece of a pass loaded before
 // any is stored, so that a pass costs one memory round trip (two passes for a
@@ -1654,25 +1749,69 @@ __device__ __forceinline__ void decode_rows(const DevMat &a, Tables<VT> &tb,
     // in flight.
     const int64_t sf = s0 < s_end ? s0 : a.num_waves - 1;  // in bounds for idle wavefronts
     LaneGeo geo = lane_geo<1>(a, sf, lane, lane_first_row<1>(a, sf, lane));
-    uint64_t wo = uniform_load(a.woff + sf), we = uniform_load(a.woff + sf + 1);
-    uint64_t dof = uniform_load(a.doff + sf), vof = uniform_load(a.voff + sf);
+    WaveSpan<false> span(a, sf);
     if (stage == 2) __syncthreads();
     if (stage) stage_tables<VT>(a, tb, Sink::col_scale(sp));
     int64_t k = 0;
     for (int64_t s = s0; s < s_end; s += stride, ++k) {
         const int64_t s1 = s + stride < s_end ? s + stride : s;
         const LaneGeo next = lane_geo<1>(a, s1, lane, lane_first_row<1>(a, s1, lane));
-        const uint64_t wo1 = uniform_load(a.woff + s1), we1 = uniform_load(a.woff + s1 + 1);
-        const uint64_t dof1 = uniform_load(a.doff + s1), vof1 = uniform_load(a.voff + s1);
-        GlobalWords src{(const char *)(a.words + wo), 4 * (we - wo)};
-        Cursor<VT> cur{0, 0, 0, a.escd + dof, (const VT *)a.escv + vof};
+        const WaveSpan<false> span1(a, s1);
+        GlobalWords src = span.words(a);
+        Cursor<VT> cur = span.template cursor<VT>(a);
         set_progress_priority(share - k, share);
         decode_wave<1, VT, Sink, GlobalWords, TF>(a, tb, s, lane, sp, src, cur, geo);
         geo = next;
-        wo = wo1;
-        we = we1;
-        dof = dof1;
-        vof = vof1;
+        span = span1;
+    }
+}
+
+// The place of workgroup `block` among `grid` when the workgroups of one XCD
+// (dispatch is round-robin) are numbered one after the other: first + pos, of
+// the blocks on its XCD; and the first of W items that falls to workgroup i
+// when they are dealt evenly in that order, floor(i W / grid).  (32-bit
+// divisions: 64-bit ones cost the start of every wavefront about a hundred
+// instructions each.  A grid has below 2^16 workgroups.)
+struct XcdShare {
+    uint32_t grid, first, pos, blocks, per, rem;
+    __device__ __forceinline__ XcdShare(uint32_t grid_, uint32_t block, uint32_t W) : grid(grid_) {
+        const uint32_t xcd = block % kNumXcd, q = grid / kNumXcd, r = grid % kNumXcd;
+        pos = block / kNumXcd;
+        blocks = q + (xcd < r ? 1u : 0u);
+        first = xcd * q + min(xcd, r);
+        per = W / grid;
+        rem = W - per * grid;
+    }
+    __device__ __forceinline__ uint32_t cut(uint32_t i) const { return i * per + i * rem / grid; }
+};
+
+// The nonzero-layout sweep over waves s0, s0 + stride, ... below s_end (share
+// of them), tables staged on the way.  A wave starts with a chain of loads
+// (offsets and lane_row, then the row list, then the first words), so the
+// first two are issued a wave ahead, and for the first wave before the tables
+// are staged.  (Touching the first wave's words and escapes there as well
+// measured 5 us slower on the pruned weight: the staging then waits for them.)
+template <typename VT, class Sink, int TF>
+__device__ __forceinline__ void decode_lanes(const DevMat &a, Tables<VT> &tb, uint32_t lane,
+                                             const typename Sink::Params &sp, int64_t s_end, int64_t s0,
+                                             int64_t stride, int64_t share) {
+    const int64_t sf = s0 < s_end ? s0 : a.num_waves - 1;  // in bounds for idle wavefronts
+    WaveSpan<(TF != 2)> span(a, sf);
+    LaneGeo geo = lane_geo<2>(a, sf, lane, lane_first_row<2>(a, sf, lane));
+    stage_tables<VT>(a, tb, Sink::col_scale(sp));
+    int64_t k = 0;
+    for (int64_t s = s0; s < s_end; s += stride, ++k) {
+        const int64_t s1 = s + stride < s_end ? s + stride : s;
+        const WaveSpan<(TF != 2)> span1(a, s1);
+        const int32_t first1 = lane_first_row<2>(a, s1, lane);
+        GlobalWords src = span.words(a);
+        Cursor<VT> cur = span.template cursor<VT>(a);
+        set_progress_priority(share - k, share);
+        decode_wave<2, VT, Sink, GlobalWords, TF>(a, tb, s, lane, sp, src, cur, geo);
+        // (on every pass: under a branch, the decoder's waits cover both paths
+        // and came out a sixth slower)
+        geo = lane_geo<2>(a, s1, lane, first1);
+        span = span1;
     }
 }
 
@@ -1681,30 +1820,27 @@ __device__ __forceinline__ void decode_rows(const DevMat &a, Tables<VT> &tb,
 template <int LAYOUT, typename VT, class Sink, int TF>
 __device__ __forceinline__ void decode_sweep(const DevMat &a, const typename Sink::Params &sp,
                                              Tables<VT> &tb) {
-    const uint32_t lane = threadIdx.x & (kWave - 1);
-    const int64_t wpb = blockDim.x / kWave;
-    const int64_t total = (int64_t)gridDim.x * wpb;
+    const uint32_t lane = threadIdx.x & (kWave - 1), wib = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t wpb = blockDim.x / kWave;
     // Workgroups are dispatched round-robin over the XCDs.  The workgroups of
     // one XCD own one contiguous share of the encoded waves, and their
     // wavefronts sweep it together (wavefront i takes waves i, i + W, ...), so
     // at any time an XCD decodes a compact window of rows and its x gathers
     // stay in that XCD's L2.  The wave index is uniform (readfirstlane).
-    const int64_t G = gridDim.x, xcd = blockIdx.x % kNumXcd, pos_in_xcd = blockIdx.x / kNumXcd;
-    const int64_t q = G / kNumXcd, rr = G % kNumXcd;
-    const int64_t xcd_blocks = q + (xcd < rr ? 1 : 0);
-    const int64_t xcd_first = xcd * q + (xcd < rr ? xcd : rr);
-    const int64_t s_begin = xcd_first * wpb * a.num_waves / total;
-    const int64_t s_end = (xcd_first + xcd_blocks) * wpb * a.num_waves / total;
-    const int64_t stride = xcd_blocks * wpb;
-    const int64_t s0 = s_begin + pos_in_xcd * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t share = s0 < s_end ? (s_end - 1 - s0) / stride + 1 : 0;  // encoded waves of this wavefront
+    const XcdShare sh(gridDim.x, blockIdx.x, (uint32_t)a.num_waves);
+    int64_t s0 = sh.cut(sh.first) + sh.pos * wpb + wib, s_end = sh.cut(sh.first + sh.blocks);
+    const int64_t stride = sh.blocks * wpb;
+    if (a.num_waves <= (int64_t)gridDim.x * wpb) {
+        // no more waves than wavefronts: neighbouring waves to each workgroup,
+        // the same number to all (taken in order, the first workgroups would
+        // be full and the last idle)
+        s0 = sh.cut(sh.first + sh.pos) + wib;
+        s_end = sh.cut(sh.first + sh.pos + 1);
+    }
+    // encoded waves of this wavefront
+    const int64_t share = s0 < s_end ? (uint32_t)(s_end - 1 - s0) / (uint32_t)stride + 1 : 0;
     if constexpr (LAYOUT == 2) {
-        stage_tables<VT>(a, tb, Sink::col_scale(sp));
-        // long lanes: a wave's start-up is a small part of its work
-        for (int64_t s = s0, k = 0; s < s_end; s += stride, ++k) {
-            set_progress_priority(share - k, share);
-            decode_slice_global<LAYOUT, VT, Sink, TF>(a, tb, s, lane, sp);
-        }
+        decode_lanes<VT, Sink, TF>(a, tb, lane, sp, s_end, s0, stride, share);
     } else {
         decode_rows<VT, Sink, TF>(a, tb, lane, sp, s_end, s0, stride, share);
     }
@@ -1772,13 +1908,9 @@ __global__ __launch_bounds__(1024, 4) void trans_lds_kernel(DevMat a,
     const int64_t groups = (gridDim.x - (uint32_t)pb + tp.passes - 1) / (uint32_t)tp.passes;  // of this pass
     const int64_t stride = groups * wpb;
     const int64_t s0 = blockIdx.x / (uint32_t)tp.passes * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t share = s0 < a.num_waves ? (a.num_waves - 1 - s0) / stride + 1 : 0;
+    const int64_t share = s0 < a.num_waves ? (uint32_t)(a.num_waves - 1 - s0) / (uint32_t)stride + 1 : 0;
     if constexpr (LAYOUT == 2) {
-        stage_tables<VT>(a, tb, 1u);
-        for (int64_t s = s0, k = 0; s < a.num_waves; s += stride, ++k) {
-            set_progress_priority(share - k, share);
-            decode_slice_global<LAYOUT, VT, Sink, TF>(a, tb, s, lane, q);
-        }
+        decode_lanes<VT, Sink, TF>(a, tb, lane, q, a.num_waves, s0, stride, share);
     } else {
         decode_rows<VT, Sink, TF>(a, tb, lane, q, a.num_waves, s0, stride, share);
     }
@@ -1835,9 +1967,8 @@ __global__ __launch_bounds__(1024, 4) void sym_kernel(DevMat a, typename SymSink
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const int64_t wpb = blockDim.x / kWave;
     // neighbouring runs on the same XCD, as in decode_sweep
-    const int64_t G = gridDim.x, xcd = blockIdx.x % kNumXcd, qq = G / kNumXcd, rr = G % kNumXcd;
-    const int64_t pos = xcd * qq + (xcd < rr ? xcd : rr) + blockIdx.x / kNumXcd;
-    const int64_t begin = pos * a.num_waves / G, end = (pos + 1) * a.num_waves / G;
+    const XcdShare sh(gridDim.x, blockIdx.x, (uint32_t)a.num_waves);
+    const int64_t begin = sh.cut(sh.first + sh.pos), end = sh.cut(sh.first + sh.pos + 1);
     const int64_t rounds = (end - begin + wpb - 1) / wpb;
     int64_t s = begin + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     // row layout: the next wave's geometry and offsets are loaded while this
@@ -1848,9 +1979,9 @@ __global__ __launch_bounds__(1024, 4) void sym_kernel(DevMat a, typename SymSink
     for (int64_t i = 0; i < rounds; ++i, s += wpb) {
         if (s < end) {
             const LaneGeo next = lane_geo<LAYOUT>(a, clamp(s + wpb), lane, lane_first_row<LAYOUT>(a, clamp(s + wpb), lane));
-            const uint64_t wo = uniform_load(a.woff + s), we = uniform_load(a.woff + s + 1);
-            GlobalWords src{(const char *)(a.words + wo), 4 * (we - wo)};
-            Cursor<VT> cur{0, 0, 0, a.escd + uniform_load(a.doff + s), (const VT *)a.escv + uniform_load(a.voff + s)};
+            const WaveSpan<false> span(a, s);
+            GlobalWords src = span.words(a);
+            Cursor<VT> cur = span.template cursor<VT>(a);
             decode_slice<LAYOUT, VT, SymSink<VT>, GlobalWords, TF>(a, tb, s, lane, q, src, cur, geo);
             geo = next;
         }
@@ -1897,8 +2028,8 @@ __global__ __launch_bounds__(1024, MINW) void ring_kernel(DevMat a, typename Sin
     int32_t fr1 = sa + 1 < sb ? lane_first_row<LAYOUT>(a, sa + 1, lane) : 0;
     for (int64_t s = sa; s < sb; ++s) {
         const int32_t fr2 = s + 2 < sb ? lane_first_row<LAYOUT>(a, s + 2, lane) : 0;
-        LaneGeo next{0, 0, 0, 0, 0, 0};
-        if (s + 1 < sb) next = lane_geo<LAYOUT>(a, s + 1, lane, fr1);
+        const int64_t s1 = s + 1 < sb ? s + 1 : s;
+        const LaneGeo next = lane_geo<LAYOUT>(a, s1, lane, s + 1 < sb ? fr1 : (LAYOUT == 2 ? geo.krow : geo.row));
         decode_slice<LAYOUT, VT, Sink, RingWords<kRingWords>, TF>(a, tb, s, lane, sp, src, cur, geo);
         geo = next;
         fr1 = fr2;
@@ -2264,8 +2395,9 @@ __global__ __launch_bounds__(256) void csr_stream_kernel(CsrDev c, const int32_t
 // ------------------------------------------------------------ dispatch
 template <class T> struct TypeBox { typedef T type; };
 
-// the nonzero-balanced layout tracks rows and needs a few more registers
-constexpr int occ_nnz(int occ) { return occ > 7 ? 7 : occ; }
+// the nonzero-balanced layout tracks rows and needs more registers: six waves
+// per SIMD, which is what its workgroup shapes keep resident
+constexpr int occ_nnz(int occ) { return occ > 6 ? 6 : occ; }
 
 template <typename F>
 hipError_t for_kc(int k, int kcmax, F f);
@@ -2361,7 +2493,11 @@ Shape fit_shape(K kern, const Launch &L) {
 template <typename K, typename... Args>
 hipError_t launch_persistent(K kern, const DevMat &a, const Launch &L, hipStream_t st, Args... args) {
     const Shape sh = fit_shape(kern, L);
-    const int64_t need = (a.num_waves + sh.wpw - 1) / sh.wpw;
+    // small matrices: four encoded waves (one per SIMD) to a workgroup, up to a
+    // workgroup for every CU; its other wavefronts only help to stage the
+    // tables (31 waves of a 4096 x 4096 band, FP64: 17 us on 8 CUs, 20 us on 3)
+    const int64_t need = std::max((a.num_waves + sh.wpw - 1) / sh.wpw,
+                                  std::min<int64_t>((a.num_waves + 3) / 4, L.num_cus));
     const int64_t grid = L.fixed_shape ? L.grid : std::min<int64_t>((int64_t)L.num_cus * sh.per_cu, need);
     hipLaunchKernelGGL(kern, dim3((unsigned)std::max<int64_t>(1, grid)), dim3(64 * sh.wpw), 0, st, args...);
     return hipGetLastError();
