@@ -63,19 +63,43 @@ int device_cus(int dev) {
 // Device memory owned by a handle; freed in one place.
 struct DevBufs {
     std::vector<void *> ptrs;
+    uint8_t *pool = nullptr;  // of reserve: what is left of one allocation for several buffers
+    size_t pool_left = 0;
     ~DevBufs() { release(); }
     void release() {
         for (void *p : ptrs) (void)hipFree(p);
         ptrs.clear();
+        pool = nullptr;
+        pool_left = 0;
+    }
+    static size_t padded(size_t bytes, size_t pad = 256) { return (bytes + pad + 255) / 256 * 256; }
+    // one allocation for the uploads that follow (the sum of their padded sizes)
+    hipError_t reserve(size_t bytes) {
+        void *p = nullptr;
+        hipError_t e = hipMalloc(&p, bytes);
+        if (e != hipSuccess) return e;
+        ptrs.push_back(p);
+        pool = (uint8_t *)p;
+        pool_left = bytes;
+        return hipSuccess;
     }
     // copy `bytes` from host (or zero-fill when src is null) into a new buffer
     // padded by `pad` zero bytes
     hipError_t upload(void **dst, const void *src, size_t bytes, hipStream_t st, size_t pad = 256) {
         void *p = nullptr;
-        hipError_t e = hipMalloc(&p, bytes + pad);
-        if (e != hipSuccess) return e;
-        ptrs.push_back(p);
-        e = hipMemsetAsync(p, 0, bytes + pad, st);
+        hipError_t e = hipSuccess;
+        const size_t size = padded(bytes, pad);
+        if (size <= pool_left) {
+            p = pool;
+            pool += size;
+            pool_left -= size;
+        } else {
+            e = hipMalloc(&p, size);
+            if (e != hipSuccess) return e;
+            ptrs.push_back(p);
+        }
+        const size_t from = src ? bytes : 0;
+        e = hipMemsetAsync((uint8_t *)p + from, 0, size - from, st);
         if (e != hipSuccess) return e;
         if (src && bytes) e = hipMemcpyAsync(p, src, bytes, hipMemcpyHostToDevice, st);
         *dst = p;
@@ -253,27 +277,28 @@ dtans_status upload(dtans_matrix *h, hipStream_t st) {
     }
     void *p[18];
     if (c.sigma && !original_row_ptr(c, h->orig_row_ptr)) return set_err(DTANS_ECORRUPT, "bad row order");
-    HIP_TRY(h->bufs.upload(&p[0], h->gtab.data(), 8 * h->gtab.size(), st));
-    HIP_TRY(h->bufs.upload(&p[1], h->gval.data(), h->gval.size(), st));
-    HIP_TRY(h->bufs.upload(&p[2], c.row_ptr.data(), 4 * c.row_ptr.size(), st));
-    HIP_TRY(h->bufs.upload(&p[3], c.word_off.data(), 8 * c.word_off.size(), st));
-    HIP_TRY(h->bufs.upload(&p[4], c.escd_off.data(), 8 * c.escd_off.size(), st));
-    HIP_TRY(h->bufs.upload(&p[5], c.escv_off.data(), 8 * c.escv_off.size(), st));
-    HIP_TRY(h->bufs.upload(&p[6], c.words.data(), 4 * c.words.size(), st));
-    HIP_TRY(h->bufs.upload(&p[7], c.escd.data(), 4 * c.escd.size(), st));
-    HIP_TRY(h->bufs.upload(&p[8], escv_src, escv_bytes, st));
-    HIP_TRY(h->bufs.upload(&p[9], h->lane_row.data(), 4 * h->lane_row.size(), st));
-    HIP_TRY(h->bufs.upload(&p[10], h->split_row.data(), 4 * h->split_row.size(), st));
-    HIP_TRY(h->bufs.upload(&p[11], h->split_first.data(), 4 * h->split_first.size(), st));
-    HIP_TRY(h->bufs.upload(&p[12], h->split_last.data(), 4 * h->split_last.size(), st));
-    HIP_TRY(h->bufs.upload(&p[13], h->nzr.data(), 4 * h->nzr.size(), st));
-    HIP_TRY(h->bufs.upload(&p[14], h->empty_rows.data(), 4 * h->empty_rows.size(), st));
-    HIP_TRY(h->bufs.upload(&p[15], h->split_long.data(), 4 * h->split_long.size(), st));
-    p[16] = p[17] = nullptr;
+    struct Part {
+        const void *src;
+        size_t bytes;
+    };
+    std::vector<Part> parts = {
+        {h->gtab.data(), 8 * h->gtab.size()},           {h->gval.data(), h->gval.size()},
+        {c.row_ptr.data(), 4 * c.row_ptr.size()},       {c.word_off.data(), 8 * c.word_off.size()},
+        {c.escd_off.data(), 8 * c.escd_off.size()},     {c.escv_off.data(), 8 * c.escv_off.size()},
+        {c.words.data(), 4 * c.words.size()},           {c.escd.data(), 4 * c.escd.size()},
+        {escv_src, escv_bytes},                         {h->lane_row.data(), 4 * h->lane_row.size()},
+        {h->split_row.data(), 4 * h->split_row.size()}, {h->split_first.data(), 4 * h->split_first.size()},
+        {h->split_last.data(), 4 * h->split_last.size()}, {h->nzr.data(), 4 * h->nzr.size()},
+        {h->empty_rows.data(), 4 * h->empty_rows.size()}, {h->split_long.data(), 4 * h->split_long.size()}};
     if (c.sigma) {
-        HIP_TRY(h->bufs.upload(&p[16], c.perm.data(), 4 * c.perm.size(), st));
-        HIP_TRY(h->bufs.upload(&p[17], h->orig_row_ptr.data(), 4 * h->orig_row_ptr.size(), st));
+        parts.push_back({c.perm.data(), 4 * c.perm.size()});
+        parts.push_back({h->orig_row_ptr.data(), 4 * h->orig_row_ptr.size()});
     }
+    size_t total = 0;
+    for (const Part &q : parts) total += DevBufs::padded(q.bytes);
+    HIP_TRY(h->bufs.reserve(total));
+    p[16] = p[17] = nullptr;
+    for (size_t i = 0; i < parts.size(); ++i) HIP_TRY(h->bufs.upload(&p[i], parts[i].src, parts[i].bytes, st));
     // the copies complete before the call returns, so that products on any
     // stream find the matrix in place (the one synchronisation of a handle)
     HIP_TRY(hipStreamSynchronize(st));

@@ -330,19 +330,53 @@ __global__ __launch_bounds__(256) void enc_esc_write_kernel(EscJob J) {
     }
 }
 
-// device buffers of one encoder, freed with it
+// Device buffers of one encoder, freed with it: pieces of a few chunks of
+// growing size, since each allocation and each free (which waits for the
+// device) costs tens of microseconds and an encode takes about fifty.  Pieces
+// taken after a mark are given back by release and taken again by what
+// follows on the encoder's stream.
 struct DevBuffers {
-    std::vector<void *> ptrs;
+    struct Chunk {
+        uint8_t *p;
+        size_t size;
+    };
+    std::vector<Chunk> chunks;
+    size_t at = 0, used = 0;  // the chunk in use and its bytes taken
+    size_t grow = size_t(1) << 20;
     ~DevBuffers() {
-        for (void *p : ptrs) (void)hipFree(p);
+        for (const Chunk &c : chunks) (void)hipFree(c.p);
+    }
+    struct Mark {
+        size_t at, used;
+    };
+    Mark mark() const { return {at, used}; }
+    void release(Mark m) {
+        at = m.at;
+        used = m.used;
     }
     template <typename T>
     hipError_t alloc(T *&p, size_t count) {
-        void *v = nullptr;
-        hipError_t e = hipMalloc(&v, std::max<size_t>(1, count) * sizeof(T));
-        if (e != hipSuccess) return e;
-        ptrs.push_back(v);
-        p = (T *)v;
+        const size_t bytes = (std::max<size_t>(1, count) * sizeof(T) + 255) / 256 * 256;
+        while (at < chunks.size() && used + bytes > chunks[at].size) {
+            ++at;
+            used = 0;
+        }
+        if (at == chunks.size()) {
+            void *v = nullptr;
+            size_t size = std::max(bytes, grow);
+            hipError_t e = hipMalloc(&v, size);
+            if (e != hipSuccess && size > bytes) {
+                (void)hipGetLastError();
+                size = bytes;
+                e = hipMalloc(&v, size);
+            }
+            if (e != hipSuccess) return e;
+            chunks.push_back({(uint8_t *)v, size});
+            grow = std::min(2 * size, size_t(256) << 20);
+            used = 0;
+        }
+        p = (T *)(chunks[at].p + used);
+        used += bytes;
         return hipSuccess;
     }
 };
@@ -361,10 +395,10 @@ unsigned elem_grid(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<i
 
 // sorted (key, count) pairs of n keys of type K on the device
 template <typename K>
-std::string device_histogram(const K *keys, int64_t n, hipStream_t st, std::vector<KeyCount> &out) {
+std::string device_histogram(const K *keys, int64_t n, hipStream_t st, DevBuffers &B, std::vector<KeyCount> &out) {
     out.clear();
     if (n == 0) return "";
-    DevBuffers B;
+    const DevBuffers::Mark before = B.mark();
     K *sorted = nullptr, *uniq = nullptr;
     int32_t *counts = nullptr, *runs = nullptr;
     ENC_TRY(B.alloc(sorted, n));
@@ -392,6 +426,7 @@ std::string device_histogram(const K *keys, int64_t n, hipStream_t st, std::vect
     }
     out.resize(nr);
     for (int32_t i = 0; i < nr; ++i) out[i] = {(uint64_t)hk[i], (int64_t)hc[i]};
+    B.release(before);
     return "";
 }
 
@@ -436,10 +471,10 @@ class GpuEncoder final : public DeviceEncoder {
             if (hbad & 1) return "EUNSORTED: columns not ascending in row " + std::to_string(row);
             return "ERANGE: column index out of range in row " + std::to_string(row);
         }
-        std::string e = device_histogram(dkey_, nnz, st_, dhist);
+        std::string e = device_histogram(dkey_, nnz, st_, B_, dhist);
         if (!e.empty()) return e;
-        if (f64_) return device_histogram((const uint64_t *)vals_, nnz, st_, vhist);
-        return device_histogram((const uint32_t *)vals_, nnz, st_, vhist);
+        if (f64_) return device_histogram((const uint64_t *)vals_, nnz, st_, B_, vhist);
+        return device_histogram((const uint32_t *)vals_, nnz, st_, B_, vhist);
     }
 
     std::string streams(const AlphabetMap &da, const AlphabetMap &va, Container &c) override;
@@ -484,7 +519,7 @@ std::string GpuEncoder::streams(const AlphabetMap &da, const AlphabetMap &va, Co
         const int64_t steps = maxS > 0 ? maxS - 1 : 0;
         flag_off[w + 1] = flag_off[w] + 64 * (uint64_t)((steps + 15) / 16);
     }
-    DevBuffers B;
+    DevBuffers &B = B_;
     int32_t *ds = nullptr, *vs = nullptr, *err = nullptr, *dhv = nullptr, *vhv = nullptr;
     uint32_t *dm = nullptr, *vm = nullptr, *fl = nullptr, *wd = nullptr, *escd = nullptr;
     uint16_t *dsl = nullptr, *vsl = nullptr;
