@@ -58,3 +58,22 @@ def test_row_walk(name, dtype, distinct, options):
         ref = oracle.spmm(rp, ci, v, X)
         for c in range(k):
             assert rel_error(Y[:, c], ref[:, c], oracle.absmv(rp, ci, v, np.ascontiguousarray(X[:, c]))) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("n", [1, 2, 4095, 4096, 4097])
+@pytest.mark.parametrize("options", [{}, {"max_mult": 256}])
+def test_x_in_lds(n, options):
+    """Single FP32 vectors around the length that LDS holds beside the tables."""
+    torch = need_gpu()
+    progress("x in LDS n=%d %s" % (n, options))
+    rng = np.random.default_rng(n)
+    lens = np.minimum(rng.integers(0, 90, size=700), n)
+    rp = np.zeros(701, np.int32)
+    rp[1:] = np.cumsum(lens)
+    ci = np.concatenate([np.sort(rng.choice(n, size=L, replace=False)) for L in lens]).astype(np.int32)
+    v = rng.standard_normal(50).astype(np.float32)[rng.integers(0, 50, size=len(ci))]
+    A = P.Matrix.from_csr(rp, ci, v, n, layout="nnz", lane_nnz=32, **options)
+    x, y0 = workloads.vector(n, 3, np.float32), workloads.vector(700, 4, np.float32)
+    y = torch.from_numpy(y0.copy()).cuda()
+    A.spmv(torch.from_numpy(x).cuda(), y, alpha=1.5, beta=-0.25)
+    check_spmv(y.cpu().numpy(), rp, ci, v, x, y0, 1.5, -0.25, np.float32)
