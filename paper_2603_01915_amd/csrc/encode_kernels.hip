@@ -471,10 +471,12 @@ class GpuEncoder final : public DeviceEncoder {
             if (hbad & 1) return "EUNSORTED: columns not ascending in row " + std::to_string(row);
             return "ERANGE: column index out of range in row " + std::to_string(row);
         }
-        std::string e = device_histogram(dkey_, nnz, st_, B_, dhist);
+        // (the values first: their buffers are the larger ones with FP64, and
+        // the deltas' then fit into the chunks they leave)
+        std::string e = f64_ ? device_histogram((const uint64_t *)vals_, nnz, st_, B_, vhist)
+                             : device_histogram((const uint32_t *)vals_, nnz, st_, B_, vhist);
         if (!e.empty()) return e;
-        if (f64_) return device_histogram((const uint64_t *)vals_, nnz, st_, B_, vhist);
-        return device_histogram((const uint32_t *)vals_, nnz, st_, B_, vhist);
+        return device_histogram(dkey_, nnz, st_, B_, dhist);
     }
 
     std::string streams(const AlphabetMap &da, const AlphabetMap &va, Container &c) override;
