@@ -1149,7 +1149,7 @@ __device__ __forceinline__ uint32_t prefetch_escapes(const Cursor<VT> &c, uint32
 // with the row's [beg, end).  The nonzero layout
 // walks the list of nonempty rows ({row, end} pairs, a sentinel {m, nnz} at
 // the end), so a lane never visits empty rows (their y is written by
-// empty_rows_kernel) and crosses exactly one row per nonzero that starts one;
+// epilogue_kernel) and crosses exactly one row per nonzero that starts one;
 // it keeps the next four list entries, all that one segment can cross
 // (next_rows).  Finding the first entry takes two dependent loads (lane_row,
 // then the list), so callers issue the first a wave ahead (lane_first_row).
@@ -2183,7 +2183,7 @@ __global__ __launch_bounds__(1024, MINW) void ring_kernel(DevMat a, typename Sin
 // rows split over lanes (layout NNZ): y = alpha * (tail of the first lane +
 // heads of the following lanes) + beta * y.  A row spanning at most
 // kLongSplit (kLongSplitRuns) following lanes is summed by one thread
-// (fixup_kernel); a longer one by a whole wavefront (fixup_long_kernel, rows
+// (fixup_short); a longer one by a whole wavefront (fixup_long, rows
 // listed on the host): its lanes stride over the row's partials, one running
 // sum per column, then a butterfly reduction per column.
 constexpr int kMaxFixupCols = 32;
@@ -2208,12 +2208,11 @@ __device__ __forceinline__ void fixup_put(VT *Y, int64_t ldy, int32_t row, int c
 __device__ __forceinline__ int64_t first_run_start(int32_t a) { return ((int64_t)(a + 1) | (kWave - 1)) + 1; }
 
 template <typename VT>
-__global__ __launch_bounds__(256) void fixup_kernel(SplitRows sr, const double *partial, int KC,
-                                                    int runs, VT *Y, int64_t ldy, double alpha,
-                                                    double beta, int log_tpr) {
+__device__ __forceinline__ void fixup_short(const SplitRows &sr, const double *partial, int KC, int runs, VT *Y,
+                                            int64_t ldy, double alpha, double beta, int log_tpr, int64_t block) {
     // 2^log_tpr >= KC threads per split row, one column each (consecutive
     // threads read consecutive doubles of a partial slot)
-    const int64_t s = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> log_tpr;
+    const int64_t s = (block * blockDim.x + threadIdx.x) >> log_tpr;
     const int c = (int)(threadIdx.x & ((1u << log_tpr) - 1));
     if (s >= sr.n || c >= KC) return;
     const int32_t a = sr.first[s], b = sr.last[s];
@@ -2233,10 +2232,9 @@ __global__ __launch_bounds__(256) void fixup_kernel(SplitRows sr, const double *
 }
 
 template <typename VT>
-__global__ __launch_bounds__(256) void fixup_long_kernel(SplitRows sr, const double *partial, int KC,
-                                                         int runs, VT *Y, int64_t ldy, double alpha,
-                                                         double beta) {
-    const int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+__device__ __forceinline__ void fixup_long(const SplitRows &sr, const double *partial, int KC, int runs, VT *Y,
+                                           int64_t ldy, double alpha, double beta, int64_t block) {
+    const int64_t w = (block * blockDim.x + threadIdx.x) / kWave;
     const int lane = (int)(threadIdx.x & (kWave - 1));
     if (w >= sr.n_long) return;  // whole wavefronts
     const int64_t s = sr.longs[w];
@@ -2271,21 +2269,39 @@ __global__ __launch_bounds__(256) void fixup_long_kernel(SplitRows sr, const dou
         }
 }
 
-// both fix-up kernels for KC <= kMaxFixupCols columns of Y
+// What follows a product in the nonzero layouts, in one launch: the long split
+// rows (they take longest, so their workgroups come first), the other split
+// rows, and y = beta * y on the rows without nonzeros (never decoded).  The
+// three write different rows of Y.  (A launch each cost R-MAT scale 22 25 us
+// of 620, and smaller graphs as much.)
 template <typename VT>
-hipError_t launch_fixup(const SplitRows &sr, const double *partial, int KC, int runs, VT *Y,
-                        int64_t ldy, double alpha, double beta, hipStream_t st) {
-    if (sr.n == 0) return hipSuccess;
+__global__ __launch_bounds__(256) void epilogue_kernel(SplitRows sr, const int32_t *empty, int64_t n_empty,
+                                                       const double *partial, int KC, int runs, VT *Y, int64_t ldy,
+                                                       double alpha, double beta, int log_tpr, uint32_t long_blocks,
+                                                       uint32_t short_blocks) {
+    if (blockIdx.x < long_blocks) {
+        fixup_long<VT>(sr, partial, KC, runs, Y, ldy, alpha, beta, blockIdx.x);
+    } else if (blockIdx.x < long_blocks + short_blocks) {
+        fixup_short<VT>(sr, partial, KC, runs, Y, ldy, alpha, beta, log_tpr, blockIdx.x - long_blocks);
+    } else {
+        const int64_t i = (int64_t)(blockIdx.x - long_blocks - short_blocks) * blockDim.x + threadIdx.x;
+        if (i >= n_empty * KC) return;
+        VT *y = Y + (int64_t)empty[i / KC] * ldy + i % KC;
+        *y = beta == 0.0 ? (VT)0 : (VT)(beta * (double)*y);
+    }
+}
+
+// the epilogue for KC <= kMaxFixupCols columns of Y
+template <typename VT>
+hipError_t launch_epilogue(const SplitRows &sr, const int32_t *empty, int64_t n_empty, const double *partial, int KC,
+                           int runs, VT *Y, int64_t ldy, double alpha, double beta, hipStream_t st) {
+    if (sr.n == 0 && n_empty == 0) return hipSuccess;
     if (KC > kMaxFixupCols) return hipErrorInvalidValue;
     int lt = 0;
     while ((1 << lt) < KC) ++lt;
-    const int64_t threads = sr.n << lt;
-    hipLaunchKernelGGL(fixup_kernel<VT>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, sr,
-                       partial, KC, runs, Y, ldy, alpha, beta, lt);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || sr.n_long == 0) return e;
-    hipLaunchKernelGGL(fixup_long_kernel<VT>, dim3((unsigned)((sr.n_long + 3) / 4)), dim3(256), 0, st,
-                       sr, partial, KC, runs, Y, ldy, alpha, beta);
+    const int64_t nl = sr.n ? (sr.n_long + 3) / 4 : 0, ns = ((sr.n << lt) + 255) / 256, ne = (n_empty * KC + 255) / 256;
+    hipLaunchKernelGGL(epilogue_kernel<VT>, dim3((unsigned)(nl + ns + ne)), dim3(256), 0, st, sr, empty, n_empty,
+                       partial, KC, runs, Y, ldy, alpha, beta, lt, (uint32_t)nl, (uint32_t)ns);
     return hipGetLastError();
 }
 
@@ -2306,16 +2322,6 @@ __global__ __launch_bounds__(256) void flush_kernel(const uint4 *p, int64_t n, u
         acc ^= v.x ^ v.y ^ v.z ^ v.w;
     }
     if (acc == 0x9e3779b9u) sink[0] = acc;  // keeps the loads; the buffer is zero
-}
-
-// layout NNZ: y = beta * y on the rows without nonzeros (never decoded)
-template <typename VT>
-__global__ void empty_rows_kernel(const int32_t *rows, int64_t count, VT *Y, int KC, int64_t ldy,
-                                  double beta) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count * KC) return;
-    VT *y = Y + (int64_t)rows[i / KC] * ldy + i % KC;
-    *y = beta == 0.0 ? (VT)0 : (VT)(beta * (double)*y);
 }
 
 // ------------------------------------------------- multi-matrix launch
@@ -2567,20 +2573,12 @@ hipError_t for_kc(int k, int kcmax, F f) {
     return hipSuccess;
 }
 
-// layout NNZ after the decode: rows split over lanes, then rows without
+// layout NNZ after the decode: rows split over lanes, and rows without
 // nonzeros (both only write y)
 template <typename VT>
 hipError_t nnz_epilogue(const DevMat &a, const double *partial, int KC, VT *Y, int64_t ldy,
                         double alpha, double beta, hipStream_t st) {
-    hipError_t e = launch_fixup(a.split, partial, KC, 1, Y, ldy, alpha, beta, st);
-    if (e != hipSuccess) return e;
-    if (a.n_empty > 0) {
-        const int64_t tot = a.n_empty * KC;
-        hipLaunchKernelGGL(empty_rows_kernel<VT>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st,
-                           a.empty_rows, a.n_empty, Y, KC, ldy, beta);
-        return hipGetLastError();
-    }
-    return hipSuccess;
+    return launch_epilogue(a.split, a.empty_rows, a.n_empty, partial, KC, 1, Y, ldy, alpha, beta, st);
 }
 
 // the kernel instance for the matrix's table format
@@ -3011,7 +3009,7 @@ hipError_t csr_impl(const CsrDev &c, int k, const VT *X, int64_t ldx, VT *Y, int
                                dim3(256), 0, st, c, X + c0, ldx, Y + c0, ldy, alpha, beta, partial);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
-            return launch_fixup(c.split, partial, KC, 0, Y + c0, ldy, alpha, beta, st);
+            return launch_epilogue(c.split, (const int32_t *)nullptr, 0, partial, KC, 0, Y + c0, ldy, alpha, beta, st);
         }
         const int64_t rows_per_block = 256 / c.group;
         int64_t blocks = (c.m + rows_per_block - 1) / rows_per_block;
