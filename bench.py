@@ -646,8 +646,8 @@ def bench_sym(args, torch, P):
                             "dtans_bytes": fi["total_bytes"], "bits_per_nnz": round(fi["bits_per_nnz"], 3)},
            "half_storage": {"ms": round(hms, 6), "dtans_bytes": hi["total_bytes"] + n * 8,
                             "bits_per_nnz_triangle": round(hi["bits_per_nnz"], 3),
-                            "transpose_path": "global atomics" if n * 8 > 64 * 1024 else "LDS copies"},
-           "note": "the transposed half scatters into y with atomic adds; GFLOP/s counts the whole matrix"}
+                            "transpose_path": "one decode, both halves summed in LDS blocks of y"},
+           "note": "the blocks are added to y with atomic adds; GFLOP/s counts the whole matrix"}
     print(json.dumps(res), flush=True)
     return 0
 
