@@ -552,11 +552,6 @@ struct CoopSpmmSink {
     __device__ __forceinline__ VT *yrow(int32_t row) const {
         return p.Y + (uint64_t)(uint32_t)row * p.ldy + part * CL;
     }
-    // this lane's 16 bytes of the row of X at byte offset `off` (32-bit: X spans
-    // at most 4 GiB)
-    __device__ __forceinline__ u32x4 row_piece(uint32_t off) const {
-        return *(gptr<u32x4>)((const char *)p.X + (off + part * 16));
-    }
     __device__ __forceinline__ double *slot(int64_t stream, int kind) const {
         return p.partial + (2 * stream + (kind == kTail ? 1 : 0)) * KC + part * CL;
     }
@@ -583,34 +578,6 @@ struct CoopSpmmSink {
         // uniform test); otherwise the slots' rows stay as they are
         const bool moved = MULTI && ballot(nreal > 0 && rowk[nreal - 1] != last) != 0;
         if (MULTI && nreal > 0) last = rowk[nreal - 1];
-        // common case of the whole wavefront (a uniform test, of `moved` alone
-        // in a full step): four nonzeros in every stream, no row ends.  No
-        // masks, so that the rounds are one straight run of loads and
-        // products (pruned weight, FP32, k = 32: 180 -> 171 us).  With fewer
-        // lanes a row the run is short and its registers, at three waves per
-        // SIMD, spill: k = 8 69 -> 72 us, k = 16 97 -> 106.
-        if (G >= 8 && !ballot(nreal < 4) && !moved) {
-            constexpr int R = 4 * G;
-            u32x4 xs[2];
-            VT vv[2];
-            auto get = [&](int r) {
-                const uint32_t src = grp * G + (r >> 2);
-                vv[r & 1] = lane_value_of(v[r & 3], src);
-                xs[r & 1] = row_piece(lane_value(col[r & 3], src));
-            };
-            get(0);
-            get(1);
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                VT x[CL];
-                __builtin_memcpy(x, &xs[r & 1], 16);
-                const ACC vr = (ACC)vv[r & 1];
-                if (r + 2 < R) get(r + 2);
-#pragma unroll
-                for (int c = 0; c < CL; ++c) acc[r >> 2][c] = fma(vr, (ACC)x[c], acc[r >> 2][c]);
-            }
-            return;
-        }
         int nr[G];
 #pragma unroll
         for (int i = 0; i < G; ++i) nr[i] = (int)lane_value((uint32_t)nreal, grp * G + i);
