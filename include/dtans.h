@@ -275,7 +275,8 @@ dtans_status dtans_spmm_t(dtans_matrix *mat, int32_t k, const void *dY, int64_t 
  * device pointer; NULL for a zero diagonal).  Computes
  * y = alpha * (S x + S^T x + d .* x) + beta * y on `stream`: beta and the
  * diagonal term first, then one decode of S whose nonzeros add to y twice, so
- * the summation order is not deterministic.
+ * the summation order is not deterministic.  The sums are FP64 for either
+ * dtype; FP32 keeps them in the handle's scratch and rounds y once.
  * x and y are n-vectors in device memory and must not overlap.  DTANS_EINVAL
  * for a non-square mat, null or aliased vectors; otherwise as dtans_spmv and
  * dtans_spmm_t.  mat must not contain diagonal entries (they would count twice).

@@ -17,9 +17,11 @@
 using namespace dtans;
 
 namespace dtans {
-// sym_kernels.hip: y[i] = beta * y[i] + alpha * d[i] * x[i] (d null: beta * y[i])
-hipError_t launch_sym_start(bool f64, const void *d, const void *x, void *y, int64_t n, double alpha, double beta,
-                            hipStream_t st);
+// sym_kernels.hip: sums[i] = beta * y[i] + alpha * d[i] * x[i] (d null: beta *
+// y[i]), in y itself with FP64 or without sums; y[i] = sums[i]
+hipError_t launch_sym_start(bool f64, const void *d, const void *x, void *y, double *sums, int64_t n, double alpha,
+                            double beta, hipStream_t st);
+hipError_t launch_sym_end(const double *sums, float *y, int64_t n, hipStream_t st);
 }  // namespace dtans
 
 namespace {
@@ -131,7 +133,8 @@ struct dtans_matrix {
     std::vector<uint32_t> escv32;  // FP32 escaped values as uploaded (kept with the handle)
     std::vector<int32_t> orig_row_ptr;  // row-sorted containers: the original matrix's row pointers
     // device scratch of the products (layout NNZ partial sums, the transposed
-    // product's per-CU copies of dX); sized by dtans_to_device / dtans_reserve
+    // product's per-CU copies of dX, the FP32 symmetric product's sums); sized
+    // by dtans_to_device / dtans_reserve
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
     int32_t reserved_k = 0;
@@ -347,7 +350,7 @@ size_t scratch_need(const dtans_matrix *h, int32_t k) {
     const bool f64 = h->c.dtype == kF64;
     const size_t a = spmm_scratch_bytes(h->view, k);
     const size_t b = h->c.nnz > 0 ? spmm_t_work_bytes(h->view, f64, h->num_cus) : 0;
-    return std::max(a, b);
+    return std::max(std::max(a, b), sym_work_bytes(h->view, f64));
 }
 
 // Upload if needed, then grow the scratch to what products with up to k
@@ -884,12 +887,17 @@ dtans_status dtans_spmv_sym(dtans_matrix *mat, const void *diag, const void *x, 
     if (c.sigma) return set_err(DTANS_EUNSUPPORTED, "the symmetric product needs rows in CSR order");
     if (c.m > 0 && (!x || !y)) return set_err(DTANS_EINVAL, "null vector");
     if (x == y && c.m > 0) return set_err(DTANS_EINVAL, "y must not alias x");
-    // y = beta y + alpha d .* x, then y += alpha (S + S^T) x
+    // sums = beta y + alpha d .* x, then sums += alpha (S + S^T) x, in FP64: y
+    // itself, or the handle's scratch and rounded once into y
     const bool f64 = c.dtype == kF64;
-    hipError_t e = launch_sym_start(f64, diag, x, y, c.m, alpha, beta, st);
+    double *sums = f64 ? (double *)y : sym_work_bytes(mat->view, f64) ? (double *)mat->scratch : nullptr;
+    hipError_t e = launch_sym_start(f64, diag, x, y, sums, c.m, alpha, beta, st);
     if (e != hipSuccess) return hip_err(e, "dtans_spmv_sym start launch");
-    e = launch_sym(mat->view, f64, x, y, alpha, plan_launch(mat), st);
+    if (!sums) return DTANS_OK;  // no nonzeros
+    e = launch_sym(mat->view, f64, x, sums, alpha, plan_launch(mat), st);
     if (e != hipSuccess) return hip_err(e, "dtans_spmv_sym launch");
+    if (!f64) e = launch_sym_end(sums, (float *)y, c.m, st);
+    if (e != hipSuccess) return hip_err(e, "dtans_spmv_sym end launch");
     return DTANS_OK;
 }
 
