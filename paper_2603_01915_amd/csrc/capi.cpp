@@ -13,6 +13,7 @@
 #include "container.hpp"
 #include "dtans.h"
 #include "kernels.hpp"
+#include "launch_plan.hpp"
 
 using namespace dtans;
 
@@ -210,37 +211,9 @@ bool uses_ring(const dtans_matrix *h) {
     return h->stage == DTANS_STAGE_RING && h->c.esc_mode == 0 && 4 * (int64_t)h->c.words.size() < (1ll << 31);
 }
 
-// Default workgroup shape of the decode kernels: LDS admits 160 KiB /
-// table_bytes workgroups per CU (2 for FP64 and FP32); the registers admit
-// `per_simd` waves per SIMD (8 for the row-layout SpMV kernels, 7 for the
-// nonzero-balanced ones).  A workgroup's waves are dealt to the CU's 4 SIMDs,
-// so its size is kept a multiple of 4: with 9-wave workgroups, three per CU
-// did not all fit at 7 per SIMD and the third started only when another
-// ended.  Among workgroup counts, the most resident waves win (then the most
-// workgroups).
-void default_shape(bool f64, int per_simd, int &wpw, int &wgcu) {
-    const int table_bytes = kSlots * (8 + (f64 ? 12 : 8));
-    const int maxwg = std::max(1, 160 * 1024 / table_bytes);
-    wpw = 4;
-    wgcu = 1;
-    for (int g = maxwg; g >= 1; --g) {
-        const int w = std::min(16, (4 * per_simd / g) & ~3);
-        if (w >= 4 && w * g > wpw * wgcu) {
-            wpw = w;
-            wgcu = g;
-        }
-    }
-}
-
 Launch plan_launch(const dtans_matrix *h) {
-    const int per_simd = h->c.layout == kLayoutRow ? 8 : 7;
-    int wpw = 0, wgcu = 0;
-    default_shape(h->c.dtype == kF64, per_simd, wpw, wgcu);
-    if (h->wg_per_cu > 0) {
-        wgcu = h->wg_per_cu;
-        wpw = std::max(4, std::min(16, (4 * per_simd / wgcu) & ~3));
-    }
-    if (h->waves_per_wg > 0) wpw = h->waves_per_wg;
+    const ShapePlan sp = plan_shape(h->c.dtype == kF64, h->c.layout == kLayoutRow, h->waves_per_wg, h->wg_per_cu);
+    const int wpw = sp.waves_per_wg, wgcu = sp.wg_per_cu;
     Launch L;
     L.waves_per_wg = wpw;
     int64_t need = (h->c.num_waves + wpw - 1) / wpw;
@@ -251,7 +224,7 @@ Launch plan_launch(const dtans_matrix *h) {
     // ring kernels: 16-wave workgroups unless set, as many per CU as fit
     L.ring_waves_per_wg = h->waves_per_wg > 0 ? h->waves_per_wg : 16;
     L.wg_per_cu = h->wg_per_cu;
-    L.fixed_shape = (h->waves_per_wg > 0 || h->wg_per_cu > 0) ? 1 : 0;
+    L.fixed_shape = sp.fixed ? 1 : 0;
     return L;
 }
 
@@ -425,7 +398,7 @@ void auto_encoding(int64_t m, int64_t nnz, const int32_t *row_ptr, const dtans_e
         if (T == 0) {
             // wavefronts the SpMV launch keeps resident on 256 CUs
             int wpw = 0, wgcu = 0;
-            default_shape(f64, 7, wpw, wgcu);
+            default_shape(f64, kNnzWavesPerSimd, wpw, wgcu);
             const int64_t resident = 256LL * wpw * wgcu;
             int64_t t;
             if (maxlen <= 4 * std::max(mean, 1.0)) {
@@ -449,13 +422,13 @@ void auto_encoding(int64_t m, int64_t nnz, const int32_t *row_ptr, const dtans_e
 std::vector<std::pair<int, int>> launch_shapes(int layout, bool f64, int wpw_fixed, int wg_fixed) {
     const int table_bytes = kSlots * (8 + (f64 ? 8 : 4));
     const int maxwg = std::max(1, 160 * 1024 / table_bytes);
-    const int per_simd = layout == DTANS_LAYOUT_ROW ? 8 : 7;
+    const int per_simd = layout == DTANS_LAYOUT_ROW ? kRowWavesPerSimd : kNnzWavesPerSimd;
     std::vector<std::pair<int, int>> out;  // (waves_per_wg, wg_per_cu)
     std::vector<int> wgs;
     if (wg_fixed) {
         wgs.push_back(wg_fixed);
     } else {
-        // the library's own shape first
+        // the library's own shape first (launched as without options)
         int dw = 0, dg = 0;
         default_shape(f64, per_simd, dw, dg);
         if (!wpw_fixed) out.push_back({dw, dg});
@@ -1210,8 +1183,12 @@ dtans_status dtans_autotune(int64_t m, int64_t n, int64_t nnz, const int32_t *ro
     for (char &ch : devname)
         if (ch == ' ' || ch == '\t' || ch == '\n') ch = '_';
 
-    // fingerprint of the problem: sizes, dtype, k, the fixed options, the arrays
+    // fingerprint of the problem: sizes, dtype, k, the fixed options, the
+    // arrays, and a number raised when the kernels' relative speeds change, so
+    // that results of earlier kernels are not taken from the cache
+    constexpr uint64_t kKernelSet = 2;
     Fingerprint fp;
+    fp.word(kKernelSet);
     for (int64_t w : {m, n, nnz, (int64_t)dtype, (int64_t)k, (int64_t)inout->layout,
                       (int64_t)inout->lane_nnz, (int64_t)inout->waves_per_wg,
                       (int64_t)inout->wg_per_cu, (int64_t)inout->sort_rows,
