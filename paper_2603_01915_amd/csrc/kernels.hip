@@ -2613,7 +2613,7 @@ hipError_t launch_persistent(K kern, const DevMat &a, const Launch &L, hipStream
     // workgroup for every CU; its other wavefronts only help to stage the
     // tables (31 waves of a 4096 x 4096 band, FP64: 17 us on 8 CUs, 20 us on 3)
     const int64_t need = std::max((a.num_waves + sh.wpw - 1) / sh.wpw,
-                                  std::min<int64_t>((a.num_waves + 3) / 4, L.num_cus));
+                                  a.num_waves <= L.max_spread ? std::min<int64_t>((a.num_waves + 3) / 4, L.num_cus) : 0);
     const int64_t grid = L.fixed_shape ? L.grid : std::min<int64_t>((int64_t)L.num_cus * sh.per_cu, need);
     hipLaunchKernelGGL(kern, dim3((unsigned)std::max<int64_t>(1, grid)), dim3(64 * sh.wpw), 0, st, args...);
     return hipGetLastError();
@@ -2884,6 +2884,11 @@ hipError_t spmm_t_impl(const DevMat &a, int k, const VT *dY, int64_t lddy, VT *d
         }
         return hipSuccess;
     }
+    // The scatter is bound by global atomic adds, which more CUs at work only
+    // make contend: it spreads over them up to four waves a CU (157 waves, FP64:
+    // 27 us, 59 in full workgroups) and runs in full workgroups past that (1563
+    // waves, 60 a row, FP64: 281 us, 308 on all CUs; FP32, 40 a row: 236, 293).
+    L.max_spread = 4 * L.num_cus;
     return for_kc(k, [&](auto KCc, int c0) {
         constexpr int KC = decltype(KCc)::value;
         const int64_t tot = a.n * KC;
