@@ -1937,8 +1937,8 @@ __global__ __launch_bounds__(decode_max_threads(MINW), MINW) void decode_kernel(
     decode_sweep<LAYOUT, VT, Sink, TF>(a, sp, tb);
 }
 
-// decode_kernel for CsrOut<VT, true>: 12 waves, whose exchange takes 75 KiB of
-// LDS beside the tables, one workgroup a CU.
+// decode_kernel for CsrOut<VT, true>: up to 12 waves, whose exchange takes 75
+// KiB of LDS beside the tables, one workgroup a CU.
 constexpr int kXchWaves = 12;
 template <typename VT>
 __global__ __launch_bounds__(64 * kXchWaves, 3) void csr_rows_kernel(DevMat a, typename CsrOut<VT, true>::Params sp) {
@@ -2606,6 +2606,13 @@ Shape fit_shape(K kern, const Launch &L) {
     return best;
 }
 
+// Wavefronts of the one workgroup a CU of a kernel whose LDS admits no second
+// one: as many as a caller's shape keeps on a CU, `most` otherwise.
+int lone_group_waves(const Launch &L, int most) {
+    if (!L.fixed_shape) return most;
+    return std::min(most, L.waves_per_wg * std::max(1, (L.grid + L.num_cus - 1) / L.num_cus));
+}
+
 template <typename K, typename... Args>
 hipError_t launch_persistent(K kern, const DevMat &a, const Launch &L, hipStream_t st, Args... args) {
     const Shape sh = fit_shape(kern, L);
@@ -2943,15 +2950,23 @@ hipError_t decode_impl(const DevMat &a, int32_t *col, void *vals, Launch L, hipS
                                          decode_kernel<2, VT, DS, occ_nnz(DS::kOcc), 0>),
                                  a, L, st, a, sp);
     }
-    if (a.layout == 1 && a.base_direct && a.no_escape && !L.fixed_shape) {
+    // Rows by groups of lanes: what it saves is the stores' cache lines, what it
+    // costs is a longer walk.  So from four waves a CU on (rows of 60, FP64:
+    // 4096 waves 75 -> 60 us, 1024 waves 28 -> 24, 512 waves 21 us either way,
+    // 64 waves 17 -> 19; FP32: 67 -> 55, 25 -> 23, 17 -> 20, 14 -> 18) and where
+    // the values of a mean row fill a line's half (15625 waves, FP64: rows of 8
+    // 36 -> 30 us, of 4 19 -> 21; FP32: of 16 51 -> 41, of 8 24 -> 26).
+    if (a.layout == 1 && a.base_direct && a.no_escape && a.num_waves >= 4 * L.num_cus &&
+        a.nnz * (int64_t)sizeof(VT) >= 64 * a.m) {
         typedef CsrOut<VT, true> CX;
         const typename CX::Params sx{col, (BT *)vals, nullptr};
-        const size_t dyn = (size_t)kXchWaves * kWave * CX::kLaneWords * 4;
+        const int waves = lone_group_waves(L, kXchWaves);
+        const size_t dyn = (size_t)waves * kWave * CX::kLaneWords * 4;
         hipError_t e = hipFuncSetAttribute((const void *)csr_rows_kernel<VT>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
         if (e != hipSuccess) return e;
-        const int64_t grid = std::min<int64_t>(L.num_cus, (a.num_waves + 3) / 4);
-        hipLaunchKernelGGL(csr_rows_kernel<VT>, dim3((unsigned)grid), dim3(64 * kXchWaves), dyn, st, a, sx);
+        const int64_t grid = L.fixed_shape ? std::min(L.grid, L.num_cus) : L.num_cus;
+        hipLaunchKernelGGL(csr_rows_kernel<VT>, dim3((unsigned)grid), dim3(64 * waves), dyn, st, a, sx);
         return hipGetLastError();
     }
     typedef CsrOut<VT> CO;

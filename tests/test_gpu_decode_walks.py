@@ -42,3 +42,31 @@ def test_two_walks(layout, T, dtype, escapes, max_mult):
         r2, c2, v2 = A.decode_csr()
         assert np.array_equal(r2.cpu().numpy(), rp) and np.array_equal(c2.cpu().numpy(), ci)
         assert np.array_equal(v2.cpu().numpy().view(np.uint8), v.view(np.uint8))
+
+
+@pytest.mark.parametrize("dtype,short,long", [(np.float64, 7, 9), (np.float32, 15, 17)])
+@pytest.mark.parametrize("shape", [(0, 0), (1, 1), (4, 2), (16, 1), (16, 2)])
+def test_rows_by_groups(dtype, short, long, shape):
+    """Rows dealt to groups of lanes: from four waves a CU and a mean row whose
+    values fill 64 bytes (a little below and above that mean), row lengths
+    around the walks' eight segments in one matrix, launch shapes of the
+    caller's, a last wave of five rows."""
+    torch = need_gpu()
+    waves = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    for mean, rows in ((short, 64 * waves), (long, 64 * waves), (long, 64 * (waves - 1) + 5), (long, 64 * waves + 5)):
+        lens = np.full(rows, mean)
+        lens[:64 * 19] = np.repeat([0, 1, 2, 3, 4, 5, 27, 28, 29, 31, 32, 33, 34, 35, 36, 63, 64, 65, 100], 64)
+        lens[:64] = np.arange(64)
+        progress("rows by groups %s mean %d, %d rows, shape %s" % (dtype.__name__, mean, rows, shape))
+        rp = np.zeros(rows + 1, np.int64)
+        rp[1:] = np.cumsum(lens)
+        within = np.arange(rp[-1]) - np.repeat(rp[:-1], lens)
+        ci = (np.repeat(np.arange(rows), lens) + 2 * within).astype(np.int32)
+        v = np.array([0.5, -1.5, 2.0, 0.25], dtype)[within % 4]
+        rp, n = rp.astype(np.int32), rows + 200
+        A = P.Matrix.from_csr(rp, ci, v, n, layout="row")
+        assert A.info()["esc_delta"] == 0 and A.info()["esc_value"] == 0
+        A.set_launch(*shape)
+        r2, c2, v2 = A.decode_csr()
+        assert np.array_equal(r2.cpu().numpy(), rp) and np.array_equal(c2.cpu().numpy(), ci)
+        assert np.array_equal(v2.cpu().numpy().view(np.uint8), v.view(np.uint8))
