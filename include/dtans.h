@@ -78,7 +78,13 @@ typedef struct {
     int32_t layout;        /* dtans_layout */
     int32_t lane_nnz;      /* NNZ layout: nonzeros per lane, multiple of 4; 0 = auto */
     int32_t waves_per_wg;  /* kernel launch: wavefronts per workgroup (1..16); 0 = auto */
-    int32_t wg_per_cu;     /* kernel launch: persistent workgroups per CU; 0 = auto */
+    int32_t wg_per_cu;     /* kernel launch: persistent workgroups per CU; 0 = auto.
+                              Kernels whose LDS admits one workgroup per CU (the
+                              symmetric product, the CSR decode of long regular rows)
+                              run one of as many wavefronts as the two keep on a CU,
+                              as far as they fit; the transposed product in LDS and
+                              the batch choose their own.  The default shape given
+                              here is the automatic launch */
     int32_t sort_rows;     /* 1: sort columns within rows first (values follow) */
     int32_t stream_stage;  /* SpMV/SpMM: 0 = auto (direct), 1 = read stream words
                               directly from device memory, 2 = stage them through an

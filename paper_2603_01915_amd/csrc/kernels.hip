@@ -2931,8 +2931,9 @@ hipError_t sym_impl(const DevMat &a, const VT *x, double *y, double alpha, Launc
     if (e != hipSuccess) return e;
     // small matrices: four waves a workgroup at least, so that fewer tables
     // are staged
-    const int64_t grid = std::min<int64_t>(L.num_cus, (a.num_waves + 3) / 4);
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1024), BlockSums::kBytes, st, a, sp);
+    const int64_t grid =
+        L.fixed_shape ? std::min(L.grid, L.num_cus) : std::min<int64_t>(L.num_cus, (a.num_waves + 3) / 4);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * lone_group_waves(L, 16)), BlockSums::kBytes, st, a, sp);
     return hipGetLastError();
 }
 
