@@ -473,6 +473,15 @@ struct SpmmSink {
     }
 };
 
+// Orders a wavefront's LDS accesses before and after it as its other lanes see
+// them.  The hardware keeps a wavefront's LDS operations in order; this holds
+// the compiler to it (no instruction of its own).
+__device__ __forceinline__ void wave_exchange_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // A 32-bit value of lane `src` (all lanes of the wavefront active)
 __device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t src) {
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src << 2), (int)v);
@@ -1609,6 +1618,7 @@ __device__ __forceinline__ void decode_slice_csr(const DevMat &a, const Tables<V
                 sp.xch[lane * kL + 3 * i + 1] = w2[i];
                 sp.xch[lane * kL + 3 * i + 2] = w3[i];
             }
+            wave_exchange_fence();  // the words are read by other lanes
             const uint32_t sub = lane & ((1u << lg) - 1u), grp = lane >> lg, rows = 64u >> lg;
             for (uint32_t b = 0; b < 1u << lg; ++b) {
                 const uint32_t rl = b * rows + grp;  // the lane that decoded this group's row
@@ -1656,6 +1666,7 @@ __device__ __forceinline__ void decode_slice_csr(const DevMat &a, const Tables<V
                 const uint32_t all = lane_value(upto, ((lane & (rows - 1u)) << lg) + (1u << lg) - 1u);
                 if ((lane >> (6u - lg)) == b) col += all;
             }
+            wave_exchange_fence();  // the next segments' words come over these
             g += 4 * kBuf;
             continue;
         }
