@@ -208,7 +208,8 @@ dtans_status dtans_to_device(dtans_matrix *mat, void *stream);
  * scratch so that dtans_spmm and dtans_spmm_t with up to k right-hand sides
  * need no allocation (the nonzero-balanced layout keeps two partial sums per
  * lane and column of a pass of at most 32 columns; the transposed product
- * keeps per-CU copies of a block of dX).  Growing waits for the device
+ * keeps per-CU copies of a block of dX; the symmetric product of FP32 values
+ * one FP64 sum per row).  Growing waits for the device
  * before the smaller buffer is freed.  k >= 1; DTANS_ENOMEM / DTANS_EHIP on
  * allocation failure. */
 dtans_status dtans_reserve(dtans_matrix *mat, int32_t k, void *stream);
@@ -216,7 +217,9 @@ dtans_status dtans_reserve(dtans_matrix *mat, int32_t k, void *stream);
 /* Sizes, entropies and launch configuration. */
 dtans_status dtans_matrix_info(const dtans_matrix *mat, dtans_info *out);
 
-/* Change the launch configuration of an encoded matrix (0 keeps the value). */
+/* Change the launch configuration of an encoded matrix (0 keeps the value; the
+ * default shape, as dtans_autotune_candidates lists it first, is the automatic
+ * launch). */
 dtans_status dtans_set_launch(dtans_matrix *mat, int32_t waves_per_wg, int32_t wg_per_cu,
                               int32_t stream_stage);
 
@@ -263,11 +266,13 @@ dtans_status dtans_spmm_noalloc(dtans_matrix *mat, int32_t k, const void *X, int
 
 /*
  * Transposed product dX = alpha * A^T dY + beta * dX by decode-and-scatter of
- * the same streams.  When n x c values of dX (c up to 8) fit in LDS beside
- * the tables, every CU scatters into its own copy with LDS atomic adds and a
- * second kernel sums the copies (the copies live in the handle's scratch);
- * otherwise the scatter uses global atomic adds.  Either way the summation
- * order is not deterministic.  dY is m x k (lddy >= k), dX is n x k
+ * the same streams.  When the columns of A, in at most two blocks, fit as FP64
+ * sums into LDS beside the tables (n up to 20480 for FP64 values, 24576 for
+ * FP32), every CU scatters into a block of its own with LDS atomic adds, up to
+ * 8 columns of dY at a time (the streams are decoded once for each such pass
+ * and block), and a second kernel sums the copies, which live in the handle's
+ * scratch; otherwise the scatter uses global atomic adds.  Either way the
+ * summation order is not deterministic.  dY is m x k (lddy >= k), dX is n x k
  * (lddx >= k), device pointers.
  */
 dtans_status dtans_spmm_t(dtans_matrix *mat, int32_t k, const void *dY, int64_t lddy, void *dX,
@@ -284,8 +289,9 @@ dtans_status dtans_spmm_t(dtans_matrix *mat, int32_t k, const void *dY, int64_t 
  * the summation order is not deterministic.  The sums are FP64 for either
  * dtype; FP32 keeps them in the handle's scratch and rounds y once.
  * x and y are n-vectors in device memory and must not overlap.  DTANS_EINVAL
- * for a non-square mat, null or aliased vectors; otherwise as dtans_spmv and
- * dtans_spmm_t.  mat must not contain diagonal entries (they would count twice).
+ * for a non-square mat, null or aliased vectors, a matrix not on the current
+ * device or without the scratch of dtans_to_device; DTANS_EUNSUPPORTED for one
+ * encoded with sort_window; streams always read directly.  mat must not contain diagonal entries (they would count twice).
  */
 dtans_status dtans_spmv_sym(dtans_matrix *mat, const void *diag, const void *x, void *y, double alpha,
                             double beta, void *stream);
@@ -391,7 +397,7 @@ void dtans_rocsparse_destroy(dtans_rocsparse *rs);
  * finished), writes the fastest options to *inout and the best time per
  * multiplication to *best_ms.  cache_path (may be NULL) names a text file of
  * earlier results, one line per (matrix fingerprint, dtype, k, fixed options,
- * device name): a hit returns the stored options without encoding; a new
+ * device name, the library's kernels): a hit returns the stored options without encoding; a new
  * result is appended (a file that cannot be written gives DTANS_EIO after
  * *inout is filled).  Needs a GPU; blocks until its work is done.
  */

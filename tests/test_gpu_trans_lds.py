@@ -75,3 +75,31 @@ def test_pass_widths(layout, T, k):
 def test_columns_32_apart():
     torch = need_gpu()
     check(torch, *matrix(900, 4096, np.float64, step=32), 4096, 2, np.float64, "nnz", 32)
+
+
+@pytest.mark.parametrize("layout,T", [("row", 0), ("nnz", 32)])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_limit_of_the_blocks(layout, T, dtype):
+    """The longest dX that two column blocks hold, and one column more (global
+    atomic adds, in column chunks of 4 and 1)."""
+    torch = need_gpu()
+    for n in (2 * ROOM[dtype], 2 * ROOM[dtype] + 1):
+        progress("trans limit n=%d %s %s" % (n, layout, dtype.__name__))
+        check(torch, *matrix(1500, n, dtype), n, 5, dtype, layout, T)
+
+
+@pytest.mark.parametrize("layout,T", [("row", 0), ("nnz", 32)])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_waves_dealt_in_turn(layout, T, dtype):
+    """Encoded waves around the number of workgroups and of wavefronts a pass
+    has: one, fewer than a workgroup's 16, no multiple of either, and more
+    than one round of every wavefront."""
+    torch = need_gpu()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for rows in (1, 64 * 5, 64 * 33 + 1, 64 * 130):
+        progress("trans waves %d rows %s %s" % (rows, layout, dtype.__name__))
+        check(torch, *matrix(rows, 257, dtype), 257, 3, dtype, layout, T)
+    # one nonzero a row: 17 waves for every wavefront of a CU's workgroup
+    m, n = 64 * (16 * cus + 1) + 3, 97
+    rp, ci = np.arange(m + 1, dtype=np.int32), (np.arange(m) * 31 % n).astype(np.int32)
+    check(torch, rp, ci, np.full(m, 0.5, dtype), n, 1, dtype, layout, T)
