@@ -511,7 +511,13 @@ __device__ __forceinline__ T lane_value_of(T v, uint32_t src) {
 // SpmmSink (tail and head slots; the middle pieces of a row summed per
 // wavefront into the head slot of the stretch's first stream), so the same
 // fix-up finishes them.
-template <typename VT, int G, typename ACC = double>
+//
+// STRAIGHT: a full step of a wavefront whose streams all stay in their rows
+// runs without masks, one straight run of loads and products (pruned 11008 x
+// 4096 weight, FP32, k = 32: 172 -> 163 us).  Its registers spill beside those
+// of the general step, which the straight one then has to make up for: it is a
+// variant for long rows (see spmm_impl).
+template <typename VT, int G, typename ACC = double, bool STRAIGHT = false>
 struct CoopSpmmSink {
     static constexpr bool kCoop = true;
     static constexpr bool kPairs = false;
@@ -587,6 +593,28 @@ struct CoopSpmmSink {
         // uniform test); otherwise the slots' rows stay as they are
         const bool moved = MULTI && ballot(nreal > 0 && rowk[nreal - 1] != last) != 0;
         if (MULTI && nreal > 0) last = rowk[nreal - 1];
+        if (STRAIGHT && !ballot(nreal < 4) && !moved) {  // uniform
+            constexpr int R = 4 * G;
+            u32x4 xs[2];
+            VT vv[2];
+            auto get = [&](int r) {
+                const uint32_t src = grp * G + (r >> 2);
+                vv[r & 1] = lane_value_of(v[r & 3], src);
+                xs[r & 1] = *(gptr<u32x4>)((const char *)p.X + (lane_value(col[r & 3], src) + part * 16));
+            };
+            get(0);
+            get(1);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                VT x[CL];
+                __builtin_memcpy(x, &xs[r & 1], 16);
+                const ACC vr = (ACC)vv[r & 1];
+                if (r + 2 < R) get(r + 2);
+#pragma unroll
+                for (int c = 0; c < CL; ++c) acc[r >> 2][c] = fma(vr, (ACC)x[c], acc[r >> 2][c]);
+            }
+            return;
+        }
         int nr[G];
 #pragma unroll
         for (int i = 0; i < G; ++i) nr[i] = (int)lane_value((uint32_t)nreal, grp * G + i);
@@ -2650,7 +2678,7 @@ hipError_t spmm_impl(const DevMat &a, int k, const VT *X, int64_t ldx, VT *Y, in
             return hipGetLastError();
         });
     }
-    auto launch = [&](auto sinkc, int KC, int c0) -> hipError_t {
+    auto launch_kernel = [&](auto sinkc, auto kern, int KC, int c0) -> hipError_t {
         typedef typename decltype(sinkc)::type SinkT;
         typename SinkT::Params sp;
         sp.X = X + c0;
@@ -2660,15 +2688,35 @@ hipError_t spmm_impl(const DevMat &a, int k, const VT *X, int64_t ldx, VT *Y, in
         sp.partial = partial;
         sp.alpha = alpha;
         sp.beta = beta;
-        hipError_t e = a.layout == 1
-                           ? launch_persistent(pick_bd(a, decode_kernel<1, VT, SinkT, SinkT::kOcc, 1>,
-                                                       decode_kernel<1, VT, SinkT, SinkT::kOcc, 0>),
-                                               a, L, st, a, sp)
-                           : launch_persistent(pick_bd(a, decode_kernel<2, VT, SinkT, occ_nnz(SinkT::kOcc), 1>,
-                                                       decode_kernel<2, VT, SinkT, occ_nnz(SinkT::kOcc), 0>),
-                                               a, L, st, a, sp);
+        hipError_t e = launch_persistent(kern, a, L, st, a, sp);
         if (e != hipSuccess || a.layout != 2) return e;
         return nnz_epilogue(a, partial, KC, Y + c0, ldy, alpha, beta, st);
+    };
+    auto launch = [&](auto sinkc, int KC, int c0) -> hipError_t {
+        typedef typename decltype(sinkc)::type SinkT;
+        return launch_kernel(sinkc,
+                             a.layout == 1 ? pick_bd(a, decode_kernel<1, VT, SinkT, SinkT::kOcc, 1>,
+                                                     decode_kernel<1, VT, SinkT, SinkT::kOcc, 0>)
+                                           : pick_bd(a, decode_kernel<2, VT, SinkT, occ_nnz(SinkT::kOcc), 1>,
+                                                     decode_kernel<2, VT, SinkT, occ_nnz(SinkT::kOcc), 0>),
+                             KC, c0);
+    };
+    // 32 FP32 columns of a matrix with long rows, nonzero layout.  Steps
+    // without row ends have to prevail and a wavefront's start and end, which
+    // spill, to be a small part of its work.  Against the general step, 2^25
+    // nonzeros and more: rows of 512 0.98, 1024 1.02 to 1.04, 2048 1.04 to 1.09
+    // times as fast; 22 M: rows of 512 0.97, 1024 and more 1.00 to 1.06; 6 M:
+    // 0.92 to 0.97, rows of 2048 1.05 or 0.95; rows of 4, 6 M: 0.67.
+    const bool straight = sizeof(VT) == 4 && a.layout == 2 && a.nnz >= (1ll << 24) && a.nnz >= 1024 * a.m;
+    auto launch_straight = [&](int c0) -> hipError_t {
+        if constexpr (sizeof(VT) == 4) {
+            typedef CoopSpmmSink<VT, 8, double, true> SinkT;
+            return launch_kernel(TypeBox<SinkT>(), pick_bd(a, decode_kernel<2, VT, SinkT, occ_nnz(SinkT::kOcc), 1>,
+                                                           decode_kernel<2, VT, SinkT, occ_nnz(SinkT::kOcc), 0>),
+                                 32, c0);
+        } else {
+            return hipErrorInvalidValue;  // not reached
+        }
     };
     // LDS-ring kernels: deferred products, at most 2 (FP64) / 4 (FP32) columns
     // per pass so that the deferred x values stay in registers
@@ -2788,7 +2836,7 @@ hipError_t spmm_impl(const DevMat &a, int k, const VT *X, int64_t ldx, VT *Y, in
         while (e == hipSuccess && k - c0 >= 2 * CLv) {
             const int left = k - c0;
             if (left >= 8 * CLv) {
-                e = launch(TypeBox<CoopSpmmSink<VT, 8>>(), 8 * CLv, c0);
+                e = straight ? launch_straight(c0) : launch(TypeBox<CoopSpmmSink<VT, 8>>(), 8 * CLv, c0);
                 c0 += 8 * CLv;
             } else if (left >= 4 * CLv) {
                 e = launch(TypeBox<CoopSpmmSink<VT, 4>>(), 4 * CLv, c0);
