@@ -130,6 +130,7 @@ struct dtans_matrix {
     bool uploaded = false;
     int device = -1, num_cus = 256;
     int waves_per_wg = 0, wg_per_cu = 0, stage = 0;
+    bool one_walk = false;  // see Launch
     DevMat view{};
     std::vector<uint32_t> escv32;  // FP32 escaped values as uploaded (kept with the handle)
     std::vector<int32_t> orig_row_ptr;  // row-sorted containers: the original matrix's row pointers
@@ -211,6 +212,37 @@ bool uses_ring(const dtans_matrix *h) {
     return h->stage == DTANS_STAGE_RING && h->c.esc_mode == 0 && 4 * (int64_t)h->c.words.size() < (1ll << 31);
 }
 
+// Whether the decode to CSR takes one walk rather than two (row layout).  Two
+// walks write whole cache lines together, which pays while all lanes of a wave
+// decode; one keeps 32 waves a CU resident instead of 16 and has the shorter
+// chain, which pays where the longest rows of the waves, each a serial chain,
+// take longer than writing the matrix (0.13 us a nonzero against 2.4 TB/s).
+// A million skewed rows of mean 12 to 17, FP32, longest row 100 (chains 0.8 of
+// the bound below): 105 us in two walks, 119 in one; 200 (1.2): 172, 156; 1000:
+// 546, 372; rows of 12: 52, 97.  A long row among regular ones, which leaves
+// most lanes busy, is no reason (one of 2669 in 2,000,000 of 12: 411, 465).
+// With no more waves than two walks keep resident only much longer rows count
+// (200,000 rows, longest 200: 51, 53; 2000: 289, 269; below 64 times the mean
+// 0.94 to 1.05).  Sorted rows are written apart from each other: FP64 gains by
+// one walk from the smallest matrix on (1,000,000 rows, longest 200: 181, 154;
+// 2000 rows: 34, 32).
+bool takes_one_walk(const Container &c, int num_cus) {
+    if (c.layout != kLayoutRow || c.m == 0) return false;
+    if (c.sigma && c.dtype == kF64) return true;
+    int64_t longest = 0, chains = 0;
+    for (int64_t w = 0; w < c.m; w += 64) {
+        int64_t most = 0;
+        for (int64_t i = w; i < std::min<int64_t>(c.m, w + 64); ++i)
+            most = std::max<int64_t>(most, c.row_ptr[i + 1] - c.row_ptr[i]);
+        longest = std::max(longest, most);
+        chains += most;
+    }
+    if (64 * chains < 2 * c.nnz) return false;
+    const int64_t resident = 16ll * num_cus;
+    if (c.num_waves <= resident && longest <= 64 * std::max<int64_t>(c.nnz / c.m, 4)) return false;
+    return std::max(longest, chains / resident) * 27000 > c.nnz;
+}
+
 Launch plan_launch(const dtans_matrix *h) {
     const ShapePlan sp = plan_shape(h->c.dtype == kF64, h->c.layout == kLayoutRow, h->waves_per_wg, h->wg_per_cu);
     const int wpw = sp.waves_per_wg, wgcu = sp.wg_per_cu;
@@ -225,6 +257,7 @@ Launch plan_launch(const dtans_matrix *h) {
     L.ring_waves_per_wg = h->waves_per_wg > 0 ? h->waves_per_wg : 16;
     L.wg_per_cu = h->wg_per_cu;
     L.fixed_shape = sp.fixed ? 1 : 0;
+    L.one_walk = h->one_walk ? 1 : 0;
     return L;
 }
 
@@ -314,6 +347,7 @@ dtans_status upload(dtans_matrix *h, hipStream_t st) {
     v.orig_row_ptr = c.sigma ? (const int32_t *)p[17] : nullptr;
     h->device = dev;
     h->num_cus = device_cus(dev);
+    h->one_walk = takes_one_walk(c, h->num_cus);
     h->uploaded = true;
     return DTANS_OK;
 }
@@ -380,8 +414,9 @@ int64_t sell_bytes(const Container &c, int slice) {
 
 // Resolve layout AUTO and lane_nnz 0 the way dtans_encode_csr does.  One row
 // per lane unless the rows are long or irregular enough that 64-row waves
-// would be too few or badly balanced; for the nonzero layout enough lanes for
-// ~8 waves per SIMD of a 256-CU device, 32..512 nonzeros each.
+// would be too few or badly balanced; for the nonzero layout an encoded wave,
+// or four for irregular rows, for every wavefront that 256 CUs keep resident
+// (six per SIMD), 32..512 nonzeros a lane.
 void auto_encoding(int64_t m, int64_t nnz, const int32_t *row_ptr, const dtans_encode_opts &o,
                    bool f64, int &layout, int &T) {
     layout = o.layout;

@@ -934,8 +934,8 @@ struct SymSink {
     }
 };
 
-// decode to CSR: column and value bits of every nonzero (streams with escapes
-// inside them; the others take decode_slice_csr)
+// decode to CSR: column and value bits of every nonzero in one walk (see
+// decode_impl; most matrices take decode_slice_csr)
 template <typename VT>
 struct DecodeSink {
     static constexpr bool kCoop = false;
@@ -1994,7 +1994,8 @@ __global__ __launch_bounds__(64 * kXchWaves, 3) void csr_rows_kernel(DevMat a, t
 // address unit takes one at a time, then are LDS reads, and a step waits on
 // memory for its words alone (pruned 11008 x 4096 weight, FP32: 38.7 us, 41.9
 // with gathers from L2; two workgroups of 12 waves a CU either way, bound by
-// the step chain's latency and VALU issue).
+// the step chain's latency and VALU issue; the reads of x add LDS bank
+// conflicts, 5.2 M cycles in all against 3.4 M for the table lookups alone).
 template <typename VT, int MINW, int TF>
 __global__ __launch_bounds__(decode_max_threads(MINW), MINW) void decode_x_kernel(
     DevMat a, typename SpmmSink<VT, 1, true, double, 0, true>::Params sp) {
@@ -2791,7 +2792,12 @@ hipError_t spmm_impl(const DevMat &a, int k, const VT *X, int64_t ldx, VT *Y, in
         sp.pair_x = a.n >= 2;
         if constexpr (sizeof(VT) == 4) {
             // x beside the tables in every workgroup of 12 waves, two a CU
-            // (80 KiB each)
+            // (80 KiB each): where it fits it was the faster one for every
+            // matrix measured.  64 to 1,000,000 rows, 512 to 4096 columns, rows
+            // of 8, 32 and 256, scattered or in runs of up to 64 adjacent
+            // columns (where the paired gathers save most): 0.82 to 0.95 of the
+            // time with gathers from 2 M nonzeros on, and none of 110 matrices
+            // down to a single encoded wave slower than before.
             const size_t dyn = (size_t)a.n * sizeof(VT);
             if (a.layout == 2 && !L.fixed_shape && sizeof(Tables<VT>) + dyn <= 80 * 1024) {
                 typedef SpmmSink<VT, 1, true, double, 0, true> XSink;
@@ -3000,7 +3006,9 @@ template <typename VT>
 hipError_t decode_impl(const DevMat &a, int32_t *col, void *vals, Launch L, hipStream_t st) {
     if (a.nnz == 0 || a.num_waves == 0) return hipSuccess;
     typedef typename Bits<VT>::T BT;
-    if (a.esc_in_stream && !a.no_escape) {
+    // one walk for escapes inside the stream, and for rows so unequal that few
+    // lanes decode most of the time
+    if ((a.esc_in_stream && !a.no_escape) || L.one_walk) {
         typedef DecodeSink<VT> DS;
         const typename DS::Params sp{col, (BT *)vals};
         if (a.layout == 1)

@@ -51,6 +51,8 @@ struct Launch {
     int wg_per_cu = 0;  // ring kernels: resident workgroups per CU (0: as many as fit)
     int fixed_shape = 0;  // 1: waves_per_wg / grid as given; 0: the direct-read kernels pick
                           // the workgroup size that keeps the most waves resident
+    int one_walk = 0;   // 1: the CSR decode takes one walk (few lanes of a wave decode most
+                        // of the time)
     int64_t max_spread = INT64_MAX;  // matrices of more encoded waves get full workgroups,
                                      // others up to a workgroup per CU
 };

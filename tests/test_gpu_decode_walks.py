@@ -70,3 +70,50 @@ def test_rows_by_groups(dtype, short, long, shape):
         r2, c2, v2 = A.decode_csr()
         assert np.array_equal(r2.cpu().numpy(), rp) and np.array_equal(c2.cpu().numpy(), ci)
         assert np.array_equal(v2.cpu().numpy().view(np.uint8), v.view(np.uint8))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("escapes", [False, True])
+@pytest.mark.parametrize("max_mult", [255, 256])
+@pytest.mark.parametrize("longest", [256, 257, 5001])
+def test_lone_rows(dtype, escapes, max_mult, longest):
+    """One row that takes longer than all the others (one walk instead of two):
+    64 times a mean below four (256: not yet), and far beyond; short and empty
+    rows around it."""
+    need_gpu()
+    lens = np.tile([0, 1, 2, 3, 5], 1400)
+    lens[3001] = longest
+    progress("decode lone row %d %s" % (longest, dtype.__name__))
+    rp = np.zeros(len(lens) + 1, np.int32)
+    rp[1:] = np.cumsum(lens)
+    rng = np.random.default_rng(longest)
+    n = 6000 if not escapes else 1 << 20
+    ci = np.concatenate([np.sort(rng.choice(n, size=L, replace=False)) for L in lens]).astype(np.int32)
+    v = rng.standard_normal(len(ci)).astype(dtype) if escapes else rng.choice([0.5, 2.0], size=len(ci)).astype(dtype)
+    A = P.Matrix.from_csr(rp, ci, v, n, layout="row", max_mult=max_mult)
+    r2, c2, v2 = A.decode_csr()
+    assert np.array_equal(r2.cpu().numpy(), rp) and np.array_equal(c2.cpu().numpy(), ci)
+    assert np.array_equal(v2.cpu().numpy().view(np.uint8), v.view(np.uint8))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("longest,sort", [(40, 0), (400, 0), (400, 256)])
+def test_unequal_rows_many_waves(dtype, longest, sort):
+    """More waves than two walks keep resident, with short and with long chains
+    (one walk); a last wave of five rows; rows in CSR order and sorted."""
+    torch = need_gpu()
+    rows = 64 * 16 * torch.cuda.get_device_properties(0).multi_processor_count + 69
+    rng = np.random.default_rng(longest)
+    lens = rng.integers(0, 6, size=rows)
+    lens[rng.integers(0, rows, size=rows // 50)] = longest
+    progress("decode unequal rows, longest %d %s sort %d" % (longest, dtype.__name__, sort))
+    rp = np.zeros(rows + 1, np.int64)
+    rp[1:] = np.cumsum(lens)
+    within = np.arange(rp[-1]) - np.repeat(rp[:-1], lens)
+    ci = (np.repeat(rng.integers(0, 5000, size=rows), lens) + 3 * within).astype(np.int32)
+    v = rng.standard_normal(100).astype(dtype)[rng.integers(0, 100, size=len(ci))]
+    rp = rp.astype(np.int32)
+    A = P.Matrix.from_csr(rp, ci, v, 5000 + 3 * longest, layout="row", sort_window=sort)
+    r2, c2, v2 = A.decode_csr()
+    assert np.array_equal(r2.cpu().numpy(), rp) and np.array_equal(c2.cpu().numpy(), ci)
+    assert np.array_equal(v2.cpu().numpy().view(np.uint8), v.view(np.uint8))
