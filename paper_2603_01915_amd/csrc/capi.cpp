@@ -223,12 +223,14 @@ bool uses_ring(const dtans_matrix *h) {
 // most lanes busy, is no reason (one of 2669 in 2,000,000 of 12: 411, 465).
 // With no more waves than two walks keep resident only much longer rows count
 // (200,000 rows, longest 200: 51, 53; 2000: 289, 269; below 64 times the mean
-// 0.94 to 1.05).  Sorted rows are written apart from each other: FP64 gains by
-// one walk from the smallest matrix on (1,000,000 rows, longest 200: 181, 154;
-// 2000 rows: 34, 32).
+// 0.94 to 1.05).  Sorted rows are written apart from each other, and their
+// long waves come a window apart, all to the same wavefronts: one walk with
+// more waves than are resident (1,000,000 rows, longest 500, windows of 256,
+// FP32: 374, 250), FP64 from the smallest matrix on (2000 rows: 34, 32).
 bool takes_one_walk(const Container &c, int num_cus) {
     if (c.layout != kLayoutRow || c.m == 0) return false;
-    if (c.sigma && c.dtype == kF64) return true;
+    const int64_t resident = 16ll * num_cus;
+    if (c.sigma && (c.dtype == kF64 || c.num_waves > resident)) return true;
     int64_t longest = 0, chains = 0;
     for (int64_t w = 0; w < c.m; w += 64) {
         int64_t most = 0;
@@ -238,7 +240,6 @@ bool takes_one_walk(const Container &c, int num_cus) {
         chains += most;
     }
     if (64 * chains < 2 * c.nnz) return false;
-    const int64_t resident = 16ll * num_cus;
     if (c.num_waves <= resident && longest <= 64 * std::max<int64_t>(c.nnz / c.m, 4)) return false;
     return std::max(longest, chains / resident) * 27000 > c.nnz;
 }

@@ -1281,15 +1281,35 @@ __device__ __forceinline__ void slot_offsets(uint32_t w1, uint32_t w2, uint32_t 
 }
 
 // A segment's escaped deltas and values from their regions, in the order
-// (nonzero, lane): flag bits in md and mv, nreal nonzeros in this lane.  All
-// eight loads are issued before any of their values is used (a use between
-// them made the wavefront wait for memory up to eight times a segment); lanes
-// without an escape read the region's next element, or, past the last one,
-// the buffer's padding.
-template <typename VT>
+// (nonzero, lane): flag bits in md and mv, nreal nonzeros in this lane.
+// TOGETHER: all eight loads are issued before any of their values is used (a
+// use between them made the wavefront wait for memory up to eight times a
+// segment); lanes without an escape read the region's next element, or, past
+// the last one, the buffer's padding.  The values on their way take twelve
+// registers with FP64, which the row layout's kernels, at eight waves per
+// SIMD, do not have: they spilled (band of 2,000,000 rows with escaped values:
+// 56 -> 64 us), so there each load goes straight to its place.
+template <typename VT, bool TOGETHER>
 __device__ __forceinline__ void take_escapes(gptr<uint32_t> ED, gptr<VT> EV, uint32_t &dpos, uint32_t &vpos, int nreal,
                                              const uint32_t md[4], const uint32_t mv[4], uint32_t scale,
                                              uint32_t dl[4], VT v[4]) {
+    if constexpr (!TOGETHER) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool f = k < nreal && (int32_t)md[k] < 0;
+            const uint64_t mk = ballot(f);
+            if (f) dl[k] = ED[dpos + lane_prefix(mk)] * scale;
+            dpos += (uint32_t)__popcll(mk);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool f = k < nreal && (int32_t)mv[k] < 0;
+            const uint64_t mk = ballot(f);
+            if (f) v[k] = EV[vpos + lane_prefix(mk)];
+            vpos += (uint32_t)__popcll(mk);
+        }
+        return;
+    }
     uint32_t rd[4];
     VT rv[4];
     // (uniform branches: in most matrices few of the eight hold an escape)
@@ -1438,8 +1458,9 @@ __device__ __forceinline__ void decode_slice(const DevMat &a, const Tables<VT> &
                         pos += (uint32_t)sizeof(VT) * (uint32_t)__popcll(mk);
                     }
                 } else {
-                    take_escapes<VT>((gptr<uint32_t>)ED, (gptr<VT>)EV, dpos, vpos, act ? min(rem, 4) : 0, md, mv,
-                                     scale, dl, v);
+                    constexpr bool together = sizeof(VT) == 4 || LAYOUT == 2;
+                    take_escapes<VT, together>((gptr<uint32_t>)ED, (gptr<VT>)EV, dpos, vpos,
+                                               act ? min(rem, 4) : 0, md, mv, scale, dl, v);
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
@@ -1717,7 +1738,7 @@ __device__ __forceinline__ void decode_slice_csr(const DevMat &a, const Tables<V
             if constexpr (TF != 2) {
                 const uint32_t fl = md[0] | md[1] | md[2] | md[3] | mv[0] | mv[1] | mv[2] | mv[3];
                 if (ballot(nreal > 0) & ballot((int32_t)fl < 0)) {  // uniform
-                    take_escapes<VT>((gptr<uint32_t>)cur.ED, (gptr<VT>)cur.EV, dpos, vpos, nreal, md, mv, 1u, dl, v);
+                    take_escapes<VT, true>((gptr<uint32_t>)cur.ED, (gptr<VT>)cur.EV, dpos, vpos, nreal, md, mv, 1u, dl, v);
                 }
             }
             if constexpr (LAYOUT == 2) {
