@@ -76,6 +76,15 @@ struct DevBufs {
         pool_left = 0;
     }
     static size_t padded(size_t bytes, size_t pad = 256) { return (bytes + pad + 255) / 256 * 256; }
+    // a piece of what reserve allocated, as it is
+    void *take(size_t bytes) {
+        const size_t size = padded(bytes, 0);
+        if (size == 0 || size > pool_left) return nullptr;
+        void *p = pool;
+        pool += size;
+        pool_left -= size;
+        return p;
+    }
     // one allocation for the uploads that follow (the sum of their padded sizes)
     hipError_t reserve(size_t bytes) {
         void *p = nullptr;
@@ -136,9 +145,10 @@ struct dtans_matrix {
     std::vector<int32_t> orig_row_ptr;  // row-sorted containers: the original matrix's row pointers
     // device scratch of the products (layout NNZ partial sums, the transposed
     // product's per-CU copies of dX, the FP32 symmetric product's sums); sized
-    // by dtans_to_device / dtans_reserve
+    // by dtans_to_device (a piece of the matrix's own allocation) / dtans_reserve
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
+    bool scratch_in_bufs = false;
     int32_t reserved_k = 0;
 };
 
@@ -233,10 +243,11 @@ bool takes_one_walk(const Container &c, int num_cus) {
     if (c.sigma && (c.dtype == kF64 || c.num_waves > resident)) return true;
     int64_t longest = 0, chains = 0;
     for (int64_t w = 0; w < c.m; w += 64) {
-        int64_t most = 0;
-        for (int64_t i = w; i < std::min<int64_t>(c.m, w + 64); ++i)
-            most = std::max<int64_t>(most, c.row_ptr[i + 1] - c.row_ptr[i]);
-        longest = std::max(longest, most);
+        const int32_t *r = c.row_ptr.data() + w;
+        const int rows = (int)std::min<int64_t>(c.m - w, 64);
+        int32_t most = 0;
+        for (int i = 0; i < rows; ++i) most = std::max(most, r[i + 1] - r[i]);
+        longest = std::max<int64_t>(longest, most);
         chains += most;
     }
     if (64 * chains < 2 * c.nnz) return false;
@@ -260,6 +271,19 @@ Launch plan_launch(const dtans_matrix *h) {
     L.fixed_shape = sp.fixed ? 1 : 0;
     L.one_walk = h->one_walk ? 1 : 0;
     return L;
+}
+
+// FP64 sums of the FP32 symmetric product (FP64 adds into y itself)
+size_t sym_sums_bytes(const Container &c) {
+    return c.dtype == kF64 || c.m != c.n || c.sigma || c.nnz == 0 ? 0 : sizeof(double) * (size_t)c.n;
+}
+
+// scratch a product with up to k right-hand sides needs (either direction)
+size_t scratch_need(const dtans_matrix *h, int32_t k) {
+    const bool f64 = h->c.dtype == kF64;
+    const size_t a = spmm_scratch_bytes(h->view, k);
+    const size_t b = h->c.nnz > 0 ? spmm_t_work_bytes(h->view, f64, h->num_cus) : 0;
+    return std::max(std::max(a, b), sym_sums_bytes(h->c));
 }
 
 dtans_status upload(dtans_matrix *h, hipStream_t st) {
@@ -304,7 +328,19 @@ dtans_status upload(dtans_matrix *h, hipStream_t st) {
         parts.push_back({c.perm.data(), 4 * c.perm.size()});
         parts.push_back({h->orig_row_ptr.data(), 4 * h->orig_row_ptr.size()});
     }
-    size_t total = 0;
+    DevMat &v = h->view;
+    v.m = c.m;
+    v.n = c.n;
+    v.nnz = c.nnz;
+    v.num_lanes = c.num_lanes;
+    v.num_waves = c.num_waves;
+    v.lane_nnz = (int32_t)c.lane_nnz;
+    v.layout = (int32_t)c.layout;
+    h->num_cus = device_cus(dev);
+    // the scratch of one right-hand side lies behind the matrix: an allocation
+    // of its own costs 0.2 ms
+    const size_t scratch = scratch_need(h, 1);
+    size_t total = DevBufs::padded(scratch, 0);
     for (const Part &q : parts) total += DevBufs::padded(q.bytes);
     HIP_TRY(h->bufs.reserve(total));
     p[16] = p[17] = nullptr;
@@ -312,7 +348,11 @@ dtans_status upload(dtans_matrix *h, hipStream_t st) {
     // the copies complete before the call returns, so that products on any
     // stream find the matrix in place (the one synchronisation of a handle)
     HIP_TRY(hipStreamSynchronize(st));
-    DevMat &v = h->view;
+    if (!h->scratch && scratch > 0) {
+        h->scratch = h->bufs.take(scratch);
+        h->scratch_bytes = h->scratch ? scratch : 0;
+        h->scratch_in_bufs = h->scratch != nullptr;
+    }
     v.tab = (const uint64_t *)p[0];
     v.tabval = p[1];
     v.row_ptr = (const int32_t *)p[2];
@@ -333,13 +373,6 @@ dtans_status upload(dtans_matrix *h, hipStream_t st) {
     v.split.longs = (const int32_t *)p[15];
     v.split.n = (int64_t)h->split_row.size();
     v.split.n_long = (int64_t)h->split_long.size();
-    v.m = c.m;
-    v.n = c.n;
-    v.nnz = c.nnz;
-    v.num_lanes = c.num_lanes;
-    v.num_waves = c.num_waves;
-    v.lane_nnz = (int32_t)c.lane_nnz;
-    v.layout = (int32_t)c.layout;
     v.base_direct = direct ? 1 : 0;
     v.no_escape = c.dtab.has_escape || c.vtab.has_escape ? 0 : 1;
     v.first_mode = c.first_mode;
@@ -347,18 +380,9 @@ dtans_status upload(dtans_matrix *h, hipStream_t st) {
     v.row_perm = c.sigma ? (const int32_t *)p[16] : nullptr;
     v.orig_row_ptr = c.sigma ? (const int32_t *)p[17] : nullptr;
     h->device = dev;
-    h->num_cus = device_cus(dev);
     h->one_walk = takes_one_walk(c, h->num_cus);
     h->uploaded = true;
     return DTANS_OK;
-}
-
-// scratch a product with up to k right-hand sides needs (either direction)
-size_t scratch_need(const dtans_matrix *h, int32_t k) {
-    const bool f64 = h->c.dtype == kF64;
-    const size_t a = spmm_scratch_bytes(h->view, k);
-    const size_t b = h->c.nnz > 0 ? spmm_t_work_bytes(h->view, f64, h->num_cus) : 0;
-    return std::max(std::max(a, b), sym_work_bytes(h->view, f64));
 }
 
 // Upload if needed, then grow the scratch to what products with up to k
@@ -372,9 +396,10 @@ dtans_status reserve(dtans_matrix *h, int32_t k, hipStream_t st) {
     if (need > h->scratch_bytes) {
         if (h->scratch) {
             HIP_TRY(hipDeviceSynchronize());
-            HIP_TRY(hipFree(h->scratch));
+            if (!h->scratch_in_bufs) HIP_TRY(hipFree(h->scratch));
             h->scratch = nullptr;
             h->scratch_bytes = 0;
+            h->scratch_in_bufs = false;
         }
         HIP_TRY(hipMalloc(&h->scratch, need));
         h->scratch_bytes = need;
@@ -899,7 +924,7 @@ dtans_status dtans_spmv_sym(dtans_matrix *mat, const void *diag, const void *x, 
     // sums = beta y + alpha d .* x, then sums += alpha (S + S^T) x, in FP64: y
     // itself, or the handle's scratch and rounded once into y
     const bool f64 = c.dtype == kF64;
-    double *sums = f64 ? (double *)y : sym_work_bytes(mat->view, f64) ? (double *)mat->scratch : nullptr;
+    double *sums = f64 ? (double *)y : sym_sums_bytes(c) ? (double *)mat->scratch : nullptr;
     hipError_t e = launch_sym_start(f64, diag, x, y, sums, c.m, alpha, beta, st);
     if (e != hipSuccess) return hip_err(e, "dtans_spmv_sym start launch");
     if (!sums) return DTANS_OK;  // no nonzeros
@@ -927,7 +952,7 @@ dtans_status dtans_decode_csr(dtans_matrix *mat, int32_t *row_ptr, int32_t *col_
 
 void dtans_destroy(dtans_matrix *mat) {
     if (!mat) return;
-    if (mat->scratch) (void)hipFree(mat->scratch);
+    if (mat->scratch && !mat->scratch_in_bufs) (void)hipFree(mat->scratch);
     delete mat;
 }
 

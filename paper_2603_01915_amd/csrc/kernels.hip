@@ -3150,10 +3150,6 @@ hipError_t launch_spmm_t(const DevMat &a, bool f64, int k, const void *dY, int64
                               work, work_bytes, st);
 }
 
-size_t sym_work_bytes(const DevMat &a, bool f64) {
-    return f64 || a.m != a.n || a.row_perm || a.nnz == 0 ? 0 : sizeof(double) * (size_t)a.n;
-}
-
 hipError_t launch_sym(const DevMat &a, bool f64, const void *x, double *y, double alpha, Launch L, hipStream_t st) {
     return f64 ? sym_impl<double>(a, (const double *)x, y, alpha, L, st)
                : sym_impl<float>(a, (const float *)x, y, alpha, L, st);

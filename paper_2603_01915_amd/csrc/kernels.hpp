@@ -83,8 +83,7 @@ hipError_t launch_spmm_t(const DevMat &a, bool f64, int k, const void *dY, int64
                          int64_t lddx, double alpha, double beta, Launch L, void *work,
                          size_t work_bytes, hipStream_t st);
 // y += alpha (S + S^T) x, S this (square) matrix of `f64` or FP32 values; y is
-// FP64 for both (FP32: sym_work_bytes of scratch, 0 where y itself serves)
-size_t sym_work_bytes(const DevMat &a, bool f64);
+// FP64 for both
 hipError_t launch_sym(const DevMat &a, bool f64, const void *x, double *y, double alpha, Launch L, hipStream_t st);
 // decode to CSR (col / raw value bits); row_ptr copied by the caller
 hipError_t launch_decode(const DevMat &a, bool f64, int32_t *col, void *vals, Launch L,
