@@ -1568,10 +1568,10 @@ __device__ __forceinline__ void decode_slice(const DevMat &a, const Tables<VT> &
 // memory, but one segment is only 16 bytes of columns and 16 or 32 of values:
 // stored segment by segment, every cache line is written in pieces too far
 // apart in time for the L2 to put together (27-point stencil on 100^3, FP64:
-// 868 MB written for 317 MB of CSR, 0.27 ms).  So kBuf segments are decoded in
+// 0.9 to 1.0 GB written for 317 MB of CSR, 0.27 ms).  So kBuf segments are decoded in
 // two walks: the first follows the stream's serial chain with the tables'
 // metadata alone and keeps each segment's three words; the second looks their
-// columns and values up and stores them, all within a short time (555 MB,
+// columns and values up and stores them, all within a short time (568 MB,
 // 0.18 ms: still bound by what the lines' pieces cost).  Escapes
 // stay in their regions until the second walk (in-stream escapes, whose
 // positions the first walk would need, take decode_slice with DecodeSink).
@@ -1580,7 +1580,7 @@ __device__ __forceinline__ void decode_slice(const DevMat &a, const Tables<VT> &
 // so even together they cost an instruction 64 cache lines, most of them in
 // part.  The second walk instead gives 2^lg lanes to a row, a segment each
 // (the words pass through LDS, the columns by a scan over the group), so that
-// an instruction stores whole rows one after the other: 0.18 -> 0.13 ms, 312 MB
+// an instruction stores whole rows one after the other: 0.18 -> 0.13 ms, 320 MB
 // written.
 template <int LAYOUT, typename VT, class Src, int TF, bool XCH>
 __device__ __forceinline__ void decode_slice_csr(const DevMat &a, const Tables<VT> &tb, int64_t slice, uint32_t lane,
@@ -2056,8 +2056,9 @@ struct TransPlan {
 // copies to sum are then as many per pass as it has workgroups, and the
 // tables are staged once per workgroup.  Bound by decoding the streams once
 // per pass and by the LDS atomic adds (see TransLdsSink): pruned 11008 x 4096
-// weight, k = 16, 6 passes of up to 3 columns: 0.365 ms, reduction 5 us (FP32
-// adds in 4 passes of 4 columns: 4 x 0.64 ms, reductions 4 x 12 us).
+// weight, k = 16, 6 passes of up to 3 columns: 0.356 ms, 31% of it bank
+// conflicts in the LDS, reduction 5 us (FP32 adds in 4 passes of 4 columns: 4 x
+// 0.64 ms, reductions 4 x 12 us).
 template <int LAYOUT, typename VT, int KC, int TF>
 __global__ __launch_bounds__(1024, 4) void trans_lds_kernel(DevMat a,
                                                             typename TransLdsSink<VT, KC>::Params sp,
