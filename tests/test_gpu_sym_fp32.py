@@ -71,3 +71,44 @@ def test_no_nonzeros():
     M.spmv_sym(torch.from_numpy(x).cuda(), torch.from_numpy(d).cuda(), y, alpha=2.0, beta=0.5)
     ref = 2.0 * d.astype(np.float64) * x + 0.5 * y0.astype(np.float64)
     assert np.all(np.abs(y.cpu().numpy() - ref) <= 2.0 ** -24 * np.abs(ref) + 2.0 ** -37 * (2 * np.abs(d * x) + np.abs(y0)))
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_captured(dtype):
+    """Replays of a captured product, with eager products of another vector and
+    the handle's other products (which use the same scratch) between them."""
+    torch = need_gpu()
+    n = 5000
+    r, c = random_upper(n, 7, 900)
+    U = sp.csr_matrix((np.ones(len(r)), (r, c)), shape=(n, n))
+    U.sum_duplicates()
+    U.sort_indices()
+    rng = np.random.default_rng(3)
+    v = rng.standard_normal(200).astype(dtype)[rng.integers(0, 200, size=U.nnz)]
+    progress("sym captured %s" % dtype.__name__)
+    M = P.Matrix.from_csr(U.indptr.astype(np.int32), U.indices.astype(np.int32), v, n, layout="nnz", lane_nnz=16)
+    M.to_device()
+    x, other = (torch.from_numpy(workloads.vector(n, i, dtype)).cuda() for i in (3, 4))
+    y = torch.zeros_like(x)
+    M.spmv_sym(x, None, y)  # loads the kernels
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        M.spmv_sym(x, None, y)
+    S = sp.csr_matrix((v.astype(np.float64), U.indices, U.indptr), shape=(n, n))
+    A = (S + S.T).tocsr()
+    A.sort_indices()
+    rp, ci = A.indptr.astype(np.int32), A.indices.astype(np.int32)
+    for i in range(4):
+        x.copy_(torch.from_numpy(workloads.vector(n, 10 + i, dtype)))
+        y.fill_(float("nan"))
+        graph.replay()
+        M.spmv_sym(other)
+        M.spmm_t(other[:, None].contiguous())
+        M.spmv(other)
+        torch.cuda.synchronize()
+        xs = x.cpu().numpy().astype(np.float64)
+        ref = oracle.spmv(rp, ci, A.data, xs)
+        unit = 2.0 ** -24 if dtype == np.float32 else 2.0 ** -53
+        bound = unit * np.abs(ref) + (2.0 ** -37 if dtype == np.float32 else 1e-12) * oracle.absmv(rp, ci, A.data, xs)
+        assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - ref) <= bound), i
